@@ -315,10 +315,8 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
         def step():
             hpr.semantic_chunk(E, off, thr, ws=ws, out=out)
 
-        ranges = (n + 127) // 128
-        # every row read once (plus one halo row per 128-sentence range), the cosines written
-        # and read back, the segment ids written
-        cbytes = 2.0 * dim * (n + ranges) + 4.0 * n + 4.0 * n + 4.0 * n + 8.0 * (off.numel())
+        # every row read once, the cosines written and read back, the segment ids written
+        cbytes = 2.0 * dim * n + 4.0 * n + 4.0 * n + 4.0 * n + 8.0 * (off.numel())
         cflops = 4.0 * dim * n  # a squared norm and a dot product per sentence
 
         def cpu_sample():

@@ -106,6 +106,29 @@ def test_chunking_paper_starts_on_range_edges():
         _check(E, off, thr, cos_g, seg_g, n_g)
 
 
+@pytest.mark.parametrize("n, dim", [
+    (1, 8), (3, 512), (4, 520), (5, 1024), (1023, 1032), (1024, 2048), (1025, 2056),  # row widths
+    (12288, 16), (12289, 8),    # one and two rows per wave
+    (400_003, 8),               # 32 rows per wave, the group counts summed by the id pass
+    (524_289, 8),               # one group more than it sums: offsets scanned first
+    (1_048_577, 8),             # 64 rows per wave
+])
+def test_chunking_range_sizes(n, dim):
+    # every rows-per-wave step and row width, papers starting on and beside the range edges
+    g = torch.Generator().manual_seed(n)
+    E = synth.unit_rows(n, dim, g, "cpu", torch.float16)
+    E[1::2] = E[0::2][: E[1::2].shape[0]]
+    cuts = {0, n} | {c + e for c in (1, 4, 32, 64, 128, 1024, n // 2) for e in (-1, 0, 1)
+                     if 0 <= c + e <= n}
+    off = torch.tensor(sorted(cuts), dtype=torch.int64)
+    cos_g, seg_g, n_g = _run(E, off, 0.9)
+    _check(E, off, 0.9, cos_g, seg_g, n_g)
+    cos_1, seg_1, n_1 = _run(E, None, 0.9)
+    _check(E, None, 0.9, cos_1, seg_1, n_1)
+    nan = np.isnan(cos_g)  # the layout changes no cosine's bits
+    assert np.array_equal(cos_1[~nan], cos_g[~nan])
+
+
 def test_chunking_zero_vectors_and_single_sentence():
     E = torch.zeros((5, 16), dtype=torch.float16)
     E[0, 0] = 1.0
