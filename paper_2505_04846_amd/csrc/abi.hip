@@ -185,7 +185,9 @@ hpr_status run_maxsim(const uint16_t* q, int32_t nq, int32_t lq, const uint16_t*
     }
   }
   hipError_t e = hipSuccess;
-  if (!amax) {  // the argmax kernel finds its own ranges (one round of workgroups)
+  if (plan.own_ranges) {
+    part = nullptr;
+  } else {
     e = timed("partition", stream, [&] {
       return launch_partition(d_off, n_docs, n_tok, plan.n_ranges, part, ctrl, n_ctrl, stream);
     });
@@ -380,7 +382,11 @@ hpr_status maxsim_score_noalloc(const uint16_t* q, int32_t nq, int32_t lq, const
     n_sync = 8 * maxsim_passes(plan);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_partition(d_off, n_docs, n_tok, plan.n_ranges, part, sync, n_sync, s);
+  hipError_t e = hipSuccess;
+  if (plan.own_ranges)
+    part = nullptr;
+  else
+    e = launch_partition(d_off, n_docs, n_tok, plan.n_ranges, part, sync, n_sync, s);
   if (e != hipSuccess) return hip_fail(e, "partition launch");
   for (int pass = 0; pass < maxsim_passes(plan) && e == hipSuccess; ++pass)
     e = launch_maxsim(plan, pass, q, nq, lq, d_tok, d_off, n_docs, n_tok, dim, part, scores,

@@ -22,6 +22,7 @@ struct MaxsimPlan {
   int qpw;         // queries per wave
   int n_qgroups;   // workgroups along the query axis
   int n_ranges;    // document ranges (workgroups along the document axis)
+  bool own_ranges; // the workgroups find their ranges themselves (no range table)
   bool persist;    // score kernel: one range per XCD, one launch of one resident round per pass
                    // of query groups
   int64_t grid;    // workgroups per launch
@@ -38,9 +39,9 @@ hipError_t launch_partition(const int64_t* off, int64_t n_docs, int64_t n_tok, i
 
 // MaxSim scores (and, when amax != nullptr, the lowest-index argmax token per (q, i, d), stored
 // as uint16 [n_docs, nq * lq]).  Without amax the kernel reads the range table `part` of
-// launch_partition.  With amax it finds its ranges itself (part is not read), zeroes
-// ctrl[0 .. n_ctrl) (the control words of the later kernels of the call; ctrl may be null), and
-// scores a document longer than 65536 tokens as NaN.
+// launch_partition, unless plan.own_ranges (part is then null).  With amax it finds its ranges
+// itself, zeroes ctrl[0 .. n_ctrl) (the control words of the later kernels of the call; ctrl may
+// be null), and scores a document longer than 65536 tokens as NaN.
 // Launches per call of the score kernel (passes of a persistent plan; 1 otherwise); pass p
 // of launch_maxsim scores query groups [p G / 8, (p + 1) G / 8) of a persistent plan.
 int maxsim_passes(const MaxsimPlan& plan);

@@ -126,8 +126,16 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
   }
   rng = __builtin_amdgcn_readfirstlane(rng);
   qg = __builtin_amdgcn_readfirstlane(qg);
-  const int d_begin = __builtin_amdgcn_readfirstlane((int)part[rng]);
-  const int d_end = __builtin_amdgcn_readfirstlane((int)part[rng + 1]);
+  // the range's documents: from the partition kernel's table, or found here (plan.own_ranges)
+  int d_begin, d_end;
+  if (part) {
+    d_begin = __builtin_amdgcn_readfirstlane((int)part[rng]);
+    d_end = __builtin_amdgcn_readfirstlane((int)part[rng + 1]);
+  } else {
+    const int first = range_first_doc(off, a.n_docs, a.n_tok, a.n_ranges, rng, lane);
+    d_begin = __builtin_amdgcn_readlane(first, 0);
+    d_end = __builtin_amdgcn_readlane(first, 32);
+  }
   if (d_begin >= d_end || qg >= a.n_qgroups) return;  // uniform for the whole workgroup
   const int qwg = qg * WPW * a.qpw;  // first query of the workgroup
   const int q0 = qwg + wave * a.qpw;
@@ -537,33 +545,52 @@ hipError_t launch_variant(const MaxsimPlan& plan, const MaxsimArgs& args, bool a
 using namespace msim;
 
 constexpr int64_t kMaxRangeTokens = 262144;  // 64 MiB of bf16 tokens at dim 128
+// Of the ranges of a call that would leave CUs idle with ranges of 1,024 tokens.  One query of
+// 32 tokens against 1,000 documents (208,000 tokens) takes 14 us a call, most of it the host's,
+// against 33 with 203 ranges; 32, 64 and 256 tokens measured the same within 1 us.
+constexpr int64_t kMinRangeTokens = 128;
 
 bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool argmax, int n_cu,
                  MaxsimPlan* p) {
   if (dim < 8 || dim > 256 || dim % 8 != 0 || lq < 1 || nq < 1 || n_docs < 1) return false;
   p->ks = dim <= 32 ? 2 : dim <= 64 ? 4 : dim <= 128 ? 8 : 16;
   p->nb = argmax ? (p->ks == 16 ? 1 : 2) : (p->ks == 16 ? 2 : 4);
+  p->lqp = (lq + 31) / 32 * 32;
+  p->wpw = 4;
+  const int lqb = p->lqp / 32;
+  const int cus = n_cu > 0 ? n_cu : 256;
   if (!argmax) {  // few query slots: fewer blocks per wave (never fewer than one query needs)
-    const int lqb = (lq + 31) / 32;
-    const int64_t slots = (int64_t)nq * lqb * 32;
+    const int64_t slots = (int64_t)nq * p->lqp;
     int need = slots <= 32 * 4 ? 1 : slots <= 64 * 4 ? 2 : 4;
     if (need < lqb) need = lqb;
     need = need <= 1 ? 1 : need <= 2 ? 2 : 4;
     if (need < p->nb) p->nb = need;
   }
-  p->wpw = 4;
-  p->lqp = (lq + 31) / 32 * 32;
   if (p->lqp > p->nb * 32) return false;
-  p->qpw = p->nb * 32 / p->lqp;
-  const int64_t q_per_wg = (int64_t)p->qpw * p->wpw;
-  p->n_qgroups = (int)((nq + q_per_wg - 1) / q_per_wg);
+  auto group = [&]() {  // queries per wave and query groups for nb blocks per wave
+    p->qpw = p->nb * 32 / p->lqp;
+    const int64_t q_per_wg = (int64_t)p->qpw * p->wpw;
+    p->n_qgroups = (int)((nq + q_per_wg - 1) / q_per_wg);
+    return (int64_t)cus * (argmax ? msim::argmax_resident(p->ks)
+                                  : msim::maxsim_resident(p->ks, p->nb));
+  };
+  // Ranges of the smallest allowed length, and whether the call fills one round of resident
+  // workgroups with them.  A score call that does not takes fewer query blocks per wave (more
+  // query groups, each with less to do per tile).
+  int64_t short_ranges = n_tok / kMinRangeTokens > 0 ? n_tok / kMinRangeTokens : 1;
+  if (short_ranges > n_docs) short_ranges = n_docs;
+  int64_t round = group();  // resident workgroups
+  while (!argmax && p->nb > 1 && p->nb / 2 >= lqb && p->n_qgroups * short_ranges < round) {
+    p->nb /= 2;
+    round = group();
+  }
+  const int occ = (int)(round / cus);
   // Workgroups: the plain score takes enough to fill every CU's resident slots 32 times over
   // (short ranges keep the workgroups sharing a range in step, so the range is served from L2);
   // the argmax variant, whose stores are short, takes one round of resident workgroups (fewer
-  // per-workgroup prologues).  No range is shorter than ~1024 tokens (the query operands are
-  // re-loaded by every workgroup).
-  const int occ = argmax ? msim::argmax_resident(p->ks) : msim::maxsim_resident(p->ks, p->nb);
-  const int64_t target_wg = (int64_t)(n_cu > 0 ? n_cu : 256) * occ * (argmax ? 1 : 32);
+  // per-workgroup prologues).  Past the first round no range is shorter than ~1024 tokens (the
+  // query operands are re-loaded by every workgroup); up to there, kMinRangeTokens.
+  const int64_t target_wg = round * (argmax ? 1 : 32);
   int64_t R = (target_wg + p->n_qgroups - 1) / p->n_qgroups;
   // ... and, for the score kernel, ranges of at most kMaxRangeTokens tokens: the up to 64
   // workgroups of an XCD that read one range together drift apart over a long range, after
@@ -573,8 +600,15 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     const int64_t by_len = (n_tok + kMaxRangeTokens - 1) / kMaxRangeTokens;
     if (R < by_len) R = by_len;
   }
-  const int64_t max_by_tokens = n_tok / 1024 > 0 ? n_tok / 1024 : 1;
+  int64_t max_by_tokens = (round + p->n_qgroups - 1) / p->n_qgroups;
+  if (max_by_tokens > short_ranges) max_by_tokens = short_ranges;
+  if (max_by_tokens < n_tok / 1024) max_by_tokens = n_tok / 1024;
   if (R > max_by_tokens) R = max_by_tokens;
+  // A few rounds: whole ones, on somewhat longer ranges, rather than a last one that is nearly
+  // empty (the loss at 100 queries x 800 documents took 520 workgroups for 512 slots: 345 us a
+  // step against 283; 64 x 32 queries against 1,000 documents 812: 107 us against 94).
+  if (R * p->n_qgroups > round && R * p->n_qgroups < 8 * round)
+    R = R * p->n_qgroups / round * round / p->n_qgroups;
   if (R > n_docs) R = n_docs;
   if (R > kMaxRanges) R = kMaxRanges;
   if (R < 1) R = 1;
@@ -590,6 +624,9 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
   // per MFMA (1.6-2.2 % faster at 4,096 x 64 queries; 2.4 % slower on the short-range grid).
   p->persist = false;
   p->grid = (int64_t)p->n_qgroups * p->n_ranges;
+  // One round of workgroups finds its ranges itself, which saves the partition launch; later
+  // rounds would each pay the search's latency again.
+  p->own_ranges = argmax || p->grid <= round;
   auto fits = [](int64_t groups, int slots) {
     return slots > 0 && groups >= 2 * slots && (groups % slots == 0 || groups >= 8 * slots);
   };
@@ -597,6 +634,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     const int slots = n_cu / 8 * occ;  // resident workgroups per XCD
     if (fits(p->n_qgroups, slots)) {
       p->persist = true;
+      p->own_ranges = false;
       p->n_ranges = 8;
       p->grid = (int64_t)8 * slots;
       if (p->ks == 8 && p->nb == 4 && occ % 2 == 0) {

@@ -16,7 +16,7 @@ struct MaxsimArgs {
   const uint16_t* q;
   const uint16_t* d;
   const int64_t* off;
-  const int64_t* part;  // range table of the score kernel (the argmax kernel finds its own)
+  const int64_t* part;  // range table of the score kernel; null: the workgroups find their own
   float* scores;
   uint16_t* amax;
   int32_t* ctrl;        // argmax kernel: control words of the call, zeroed by workgroup 0
@@ -44,6 +44,42 @@ struct StageDesc {
   int t0;
   uint32_t valid, last, lng;
 };
+
+// First document of token range r out of R equal ranges: the least d in [0, n_docs) with
+// off[d] >= floor(n_tok * r / R), or n_docs when there is none or r = R (documents are never
+// split; a range can be empty).  Lanes 0-31 answer for r = r0 and lanes 32-63 for r0 + 1, each
+// half by a 32-way search that keeps the answer inside [lo, hi]: a round probes the last offset
+// of each of 32 equal slices of [lo, hi); the probes below the target form a prefix (offsets
+// ascend), and its length picks the slice that holds the answer.  A span S shrinks to at most
+// ceil(S / 32) - 1 per round: two rounds for 1024 documents, four for 10^6.  Whatever the
+// offsets hold, lo stays within [0, n_docs] and every probe within [0, n_docs).
+__device__ __forceinline__ int range_first_doc(const int64_t* __restrict__ off, int64_t n_docs, int64_t n_tok,
+                               int R, int r0, int lane) {
+  const int half = lane >> 5, i = lane & 31;
+  // floor(n_tok * r / R) in 32 bits: n_tok < 2^31 and R <= 2^16, so (n_tok % R) * r < 2^32
+  const uint32_t nt = (uint32_t)n_tok, ru = (uint32_t)R, qt = nt / ru, mt = nt % ru;
+  const uint32_t r = (uint32_t)r0 + (uint32_t)half;
+  const uint32_t t0 = qt * (uint32_t)r0 + mt * (uint32_t)r0 / ru;
+  const uint32_t t1 = qt * (uint32_t)(r0 + 1) + mt * (uint32_t)(r0 + 1) / ru;
+  const int64_t target = half ? t1 : t0;
+  int64_t lo = r >= ru ? n_docs : 0, hi = n_docs;
+  while (__ballot(lo < hi)) {
+    const bool open = lo < hi;
+    const int64_t step = (hi - lo + 31) >> 5;
+    const int64_t last = hi - 1;
+    int64_t p = lo + (int64_t)(i + 1) * step - 1;
+    p = p < last ? p : last;
+    const bool below = open && off[p] < target;
+    const int c = __popc((uint32_t)(__ballot(below) >> (32 * half)));
+    if (open) {
+      const int64_t pl = lo + (int64_t)c * step - 1, ph = pl + step;
+      const int64_t nlo = c > 0 ? (pl < last ? pl : last) + 1 : lo;
+      hi = c < 32 ? (ph < last ? ph : last) : hi;
+      lo = nlo;
+    }
+  }
+  return (int)lo;
+}
 
 // Argmax keys ("tile keys") of one 32x32 tile column: the lane's 16 values v_r (r = 0..15,
 // rows ascending with r) as order-preserving integers o(v) (o(v) = bits of v for v >= 0,

@@ -123,6 +123,42 @@ def test_maxsim_scores_few_queries(nq, lq, dim, n_docs):
         check_topk(s[q], i[q], O[q], 50)
 
 
+@pytest.mark.parametrize("nq,lq,dim,n_docs,ld_max", [
+    (1, 32, 128, 1, 127),       # one range
+    (1, 32, 128, 130, 2),       # 128-token ranges of many documents each
+    (16, 32, 128, 50, 300),     # four blocks per wave cut to one to fill the chip
+    (10, 64, 128, 20, 300),     # ... to two, a 64-slot query's least
+    (3, 96, 128, 9, 100),       # three blocks per query: not cut
+    (5, 33, 256, 30, 64),
+    (1, 32, 128, 3000, 380),    # about one resident round: own ranges
+    (40, 32, 128, 1100, 380),   # between one and two rounds: cut to whole ones
+    (2, 32, 128, 9000, 380),    # several rounds: the partition table
+])
+def test_maxsim_small_grids(nq, lq, dim, n_docs, ld_max):
+    # the plans of calls that do not fill the chip with ranges of 1,024 tokens; the no-workspace
+    # entry point takes the same plan, and the plan changes no score's bits
+    g = torch.Generator().manual_seed(nq + n_docs)
+    lens = torch.randint(1, ld_max + 1, (n_docs,), generator=g).tolist()
+    Q, D, off = _ragged(7 + nq + n_docs, nq, lq, lens, dim)
+    args = _to_dev(Q, D, off)
+    S = hpr.maxsim_score(*args)
+    O = oracle.maxsim_scores(_bf(Q), _bf(D), off.numpy())
+    _assert_close(S.cpu().numpy(), O, rel=1e-4, what="scores")
+    assert torch.equal(S, hpr.maxsim_score_noalloc(*args))
+    half = (nq + 1) // 2
+    assert torch.equal(S[:half], hpr.maxsim_score(args[0][:half].contiguous(), *args[1:]))
+
+
+@pytest.mark.parametrize("nq,n_docs,ld_max", [(3, 5, 40), (24, 48, 300), (100, 800, 40)])
+def test_loss_small_grids(nq, n_docs, ld_max):
+    # argmax ranges below 1,024 tokens, and a grid cut to one whole round (13 query groups)
+    g = torch.Generator().manual_seed(nq)
+    lens = torch.randint(1, ld_max + 1, (n_docs,), generator=g).tolist()
+    Q, D, off = _ragged(nq, nq, 32, lens, 128)
+    pos = torch.randint(0, n_docs, (nq,), generator=g, dtype=torch.int32)
+    _loss_parity(Q, D, off, pos, 1.5625)
+
+
 def test_maxsim_many_ranges_and_query_groups():
     # enough documents and queries for several document ranges and query workgroups
     g = torch.Generator().manual_seed(7)
