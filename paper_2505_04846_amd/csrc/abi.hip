@@ -446,7 +446,7 @@ hpr_status coltrast_total_loss_fwd_bwd(const uint16_t* q, int32_t nq, int32_t lq
 size_t semantic_chunk_workspace_size(int64_t n, int32_t dim) {
   (void)dim;
   if (n < 1) return 0;
-  const int64_t R = chunk_groups(n);
+  const int64_t R = chunk_groups_most(n);
   return align_up((size_t)R * sizeof(int32_t)) + align_up((size_t)R * sizeof(int64_t)) +
          align_up((size_t)n * sizeof(float));
 }
@@ -472,7 +472,7 @@ hpr_status semantic_chunk(const uint16_t* emb, int64_t n, int32_t dim, const int
     return fail(HPR_ERR_WORKSPACE_TOO_SMALL, "workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver c(ws);
-  const int64_t R = chunk_groups(n);
+  const int64_t R = chunk_groups_most(n);
   int32_t* cnt = c.take<int32_t>((size_t)R * sizeof(int32_t));
   int64_t* base = c.take<int64_t>((size_t)R * sizeof(int64_t));
   float* cos_ws = c.take<float>((size_t)n * sizeof(float));

@@ -330,6 +330,11 @@ int64_t chunk_groups(int64_t n) {
   return (n + g - 1) / g;
 }
 
+int64_t chunk_groups_most(int64_t n) {
+  const int64_t per128 = (n + 127) / 128, g = chunk_groups(n);
+  return g > per128 ? g : per128;
+}
+
 hipError_t launch_semantic_chunk(const uint16_t* E, int64_t n, int dim, const int64_t* off,
                                  int64_t n_papers, float thr, float* cos_out, int32_t* cnt,
                                  int64_t* base, int32_t* seg, int64_t* n_seg,
