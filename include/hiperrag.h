@@ -299,6 +299,13 @@ hpr_status hpr_csr_validate(const int64_t* d_off, int64_t n_docs, int64_t n_tok,
  * upstream gradient to the gradients of the loss calls without a host round trip. */
 hpr_status hpr_scale_f32(float* x, int64_t n, const float* scale, void* stream);
 
+/* hpr_scale_grads_bf16 -- dq_out[i] = bf16(dq[i] * *scale) for i < n_q and dd_out[i] =
+ * bf16(dd[i] * *scale) for i < n_d, rounded to nearest even (scale is a device scalar): the
+ * backward of a loss call's inputs from its saved gradients, which stay as they are.  A pair with
+ * count 0 is skipped.  Any alignment of the elements' own sizes. */
+hpr_status hpr_scale_grads_bf16(const float* dq, int64_t n_q, uint16_t* dq_out, const float* dd,
+                                int64_t n_d, uint16_t* dd_out, const float* scale, void* stream);
+
 /* Calibration for benchmarks: what the device sustains, to report beside the published peaks.
  *   hpr_mfma_calibration  launches a kernel of 8 waves per CU, each running `iters` iterations
  *                         of four independent v_mfma_f32_32x32x16_bf16 on register operands (no

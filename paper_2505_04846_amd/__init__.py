@@ -80,6 +80,7 @@ _SIGNATURES = {
     "hpr_read_calibration": (_I32, [_P, _I64, _P, _P]),
     "hpr_csr_validate": (_I32, [_P, _I64, _I64, _P, _P, _P]),
     "hpr_scale_f32": (_I32, [_P, _I64, _P, _P]),
+    "hpr_scale_grads_bf16": (_I32, [_P, _I64, _P, _P, _I64, _P, _P, _P]),
     "hpr_kernel_timing": (_I32, [_I32]),
     "hpr_kernel_timing_read": (_I32, [ctypes.c_char_p, ctypes.POINTER(ctypes.c_double),
                                       ctypes.POINTER(ctypes.c_int64)]),
@@ -276,6 +277,20 @@ def scale_(x, scale):
     return x
 
 
+def _scaled_grads(dq, dd, scale):
+    """bf16(dq * scale) and bf16(dd * scale) (either may be None) in one launch; dq and dd stay
+    as they are.  The inputs of the losses are bf16, so this is what autograd hands on."""
+    device = (dq if dq is not None else dd).device
+    src = [None if t is None else t.contiguous() for t in (dq, dd)]
+    out = [None if t is None else torch.empty(t.shape, dtype=torch.bfloat16, device=device)
+           for t in src]
+    q, d = [0 if t is None else t.numel() for t in src]
+    with torch.cuda.device(device):
+        _check(lib().hpr_scale_grads_bf16(_ptr(src[0]), q, _ptr(out[0]), _ptr(src[1]), d,
+                                          _ptr(out[1]), _ptr(scale), _stream(device)))
+    return out
+
+
 class _ColTrastLI(torch.autograd.Function):
     @staticmethod
     def forward(ctx, Q, D, off, pos, logit_scale):
@@ -292,10 +307,10 @@ class _ColTrastLI(torch.autograd.Function):
         g = grad_out.reshape(1).to(torch.float32).contiguous()
         dq = saved.pop(0) if ctx.has[0] else None
         dd = saved.pop(0) if ctx.has[1] else None
-        # scale copies: the saved gradients stay as the forward left them, so a second backward
-        # over a retained graph scales them afresh
-        dq = scale_(dq.clone(), g) if dq is not None else None
-        dd = scale_(dd.clone(), g) if dd is not None else None
+        # the saved gradients stay as the forward left them, so a second backward over a retained
+        # graph scales them afresh
+        if dq is not None or dd is not None:
+            dq, dd = _scaled_grads(dq, dd, g)
         return dq, dd, None, None, None
 
 

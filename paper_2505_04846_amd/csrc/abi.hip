@@ -691,6 +691,20 @@ hpr_status hpr_scale_f32(float* x, int64_t n, const float* scale, void* stream) 
   return HPR_OK;
 }
 
+hpr_status hpr_scale_grads_bf16(const float* dq, int64_t n_q, uint16_t* dq_out, const float* dd,
+                                int64_t n_d, uint16_t* dd_out, const float* scale, void* stream) {
+  if (!scale) return fail(HPR_ERR_INVALID_ARG, "scale must be non-NULL");
+  if (n_q < 0 || n_d < 0) return fail(HPR_ERR_INVALID_ARG, "n_q and n_d must be >= 0");
+  if ((n_q > 0 && (!dq || !dq_out)) || (n_d > 0 && (!dd || !dd_out)))
+    return fail(HPR_ERR_INVALID_ARG, "a gradient and its output must be non-NULL");
+  if (n_q == 0 && n_d == 0) return HPR_OK;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipError_t e = timed("scale_grads", s, [&] {
+    return launch_scale_grads(dq, n_q, dq_out, dd, n_d, dd_out, scale, s);
+  });
+  return e == hipSuccess ? HPR_OK : hip_fail(e, "gradient scale launch");
+}
+
 hpr_status hpr_kernel_timing(int32_t enable) {
   g_timing_on.store(enable ? 1 : 0, std::memory_order_relaxed);
   return HPR_OK;

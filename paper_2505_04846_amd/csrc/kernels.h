@@ -108,6 +108,9 @@ hipError_t launch_contrastive(const float* Uq, const float* gsc_q, const float* 
                               hipStream_t stream);
 
 hipError_t launch_scale(float* x, int64_t n, const float* scale, hipStream_t stream);
+hipError_t launch_scale_grads(const float* dq, int64_t n_q, uint16_t* dq_out, const float* dd,
+                              int64_t n_d, uint16_t* dd_out, const float* scale,
+                              hipStream_t stream);
 
 // Dense inner-product top-k ----------------------------------------------------------------------
 // Rows [0, S) are the exact sample; candidate lists hold `cap` entries per query.

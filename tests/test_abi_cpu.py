@@ -215,6 +215,10 @@ def test_csr_validate_and_scale_reject_null():
     assert lib.hpr_csr_validate(FAKE, 0, 10, FAKE, NULL, ctypes.byref(bad)) == 1
     assert lib.hpr_scale_f32(NULL, 4, FAKE, NULL) == 1
     assert lib.hpr_scale_f32(FAKE, -1, FAKE, NULL) == 1
+    assert lib.hpr_scale_grads_bf16(FAKE, 4, FAKE, FAKE, 4, FAKE, NULL, NULL) == 1
+    assert lib.hpr_scale_grads_bf16(FAKE, -1, FAKE, FAKE, 4, FAKE, FAKE, NULL) == 1
+    assert lib.hpr_scale_grads_bf16(FAKE, 4, NULL, NULL, 0, NULL, FAKE, NULL) == 1
+    assert lib.hpr_scale_grads_bf16(NULL, 0, NULL, NULL, 0, NULL, FAKE, NULL) == 0
 
 
 def test_binding_refuses_cpu_tensors():

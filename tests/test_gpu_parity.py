@@ -539,6 +539,31 @@ def test_autograd_function_matches_fwd_bwd_and_scales():
     assert float(loss.detach()) == float(ref["loss"][0])
 
 
+@pytest.mark.parametrize("n_q,n_d,shift", [(8, 0, 0), (0, 40, 0), (64, 8 * 300_007, 0),
+                                           (7, 1000, 0), (64, 64, 1)])
+def test_scaled_gradients_equal_a_rounded_product(n_q, n_d, shift):
+    # the vector path, one array only, more values than one round of workgroups, and the
+    # value-by-value path (odd lengths, an unaligned array), with the specials bf16 rounding meets
+    g = torch.Generator().manual_seed(n_q + n_d)
+    special = torch.tensor([0.0, -0.0, float("inf"), float("-inf"), float("nan"), 1e-45, -3e-39,
+                            3.4e38, 1.00390625, 1.01171875, -1e-20])
+    scale = torch.tensor(0.37, device=DEV)
+
+    def grad(n):
+        x = torch.randn(n + shift, generator=g)
+        m = min(n, special.numel())
+        x[shift:shift + m] = special[:m]
+        return x.to(DEV)[shift:] if n else None
+
+    dq, dd = grad(n_q), grad(n_d)
+    for src, out in zip((dq, dd), hpr._scaled_grads(dq, dd, scale)):
+        if src is None:
+            assert out is None
+            continue
+        ref = (src * scale).to(torch.bfloat16)
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
 def test_autograd_second_backward_over_a_retained_graph():
     # each backward scales the forward's gradients by its own upstream gradient (the saved
     # tensors are not scaled in place, which would compound the two upstream gradients)
