@@ -323,7 +323,8 @@ size_t maxsim_topk_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_
                                   int32_t dim, int32_t k) {
   (void)lq, (void)n_tok, (void)dim, (void)k;
   if (nq < 1 || n_docs < 1) return 0;
-  return align_up((size_t)nq * (size_t)n_docs * sizeof(float)) + part_bytes(n_docs);
+  return align_up((size_t)nq * (size_t)n_docs * sizeof(float)) + part_bytes(n_docs) +
+         align_up(topk_scratch_bytes(nq, n_docs));
 }
 
 size_t coltrast_loss_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_t n_tok,
@@ -415,8 +416,9 @@ hpr_status maxsim_topk(const uint16_t* q, int32_t nq, int32_t lq, const uint16_t
   st = run_maxsim(q, nq, lq, d_tok, d_off, n_docs, n_tok, dim, scores, nullptr, nullptr, 0, part,
                   part_bytes(n_docs), s);
   if (st != HPR_OK) return st;
+  void* scratch = c.take<char>(topk_scratch_bytes(nq, n_docs));
   hipError_t e = timed("topk", s, [&] {
-    return launch_topk_rows(scores, nq, n_docs, n_docs, k, out_scores, out_idx, s);
+    return launch_topk_rows(scores, nq, n_docs, n_docs, k, out_scores, out_idx, scratch, s);
   });
   if (e != hipSuccess) return hip_fail(e, "top-k launch");
   return HPR_OK;
@@ -532,8 +534,9 @@ hpr_status hpr_read_calibration(const void* buf, int64_t bytes, uint32_t* sink, 
 
 size_t dense_ip_topk_workspace_size(int32_t nq, int64_t n, int32_t dim, int32_t k) {
   if (nq < 1 || n < 1 || dim < 1 || k < 1) return 0;
-  const DensePlan p = dense_plan(n, k);
-  size_t b = align_up((size_t)nq * (size_t)p.S * sizeof(float));  // sample scores
+  const DensePlan p = dense_plan(nq, n, k);
+  size_t b = align_up((size_t)nq * (size_t)p.S * sizeof(float)) +  // sample scores
+             align_up(topk_scratch_bytes(nq, p.S));
   if (p.S == n) return b;
   b += align_up((size_t)nq * k * sizeof(float)) + align_up((size_t)nq * k * sizeof(int64_t));
   b += align_up((size_t)nq * sizeof(float)) + align_up((size_t)nq * sizeof(int64_t)) +
@@ -570,9 +573,10 @@ hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64
   hpr_status st = current_cu_count(&n_cu);
   if (st != HPR_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const DensePlan p = dense_plan(n, k);
+  const DensePlan p = dense_plan(nq, n, k);
   Carver c(ws);
   float* sample = c.take<float>((size_t)nq * (size_t)p.S * sizeof(float));
+  void* scratch = c.take<char>(topk_scratch_bytes(nq, p.S));
   DenseGemm g = {};
   g.mode = 0;
   g.q = q;
@@ -587,7 +591,7 @@ hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64
   if (e != hipSuccess) return hip_fail(e, "dense sample launch");
   if (p.S == n) {  // the sample is the whole store
     e = timed("topk", s, [&] {
-      return launch_topk_rows(sample, nq, n, n, k, out_scores, out_idx, s);
+      return launch_topk_rows(sample, nq, n, n, k, out_scores, out_idx, scratch, s);
     });
     return e == hipSuccess ? HPR_OK : hip_fail(e, "top-k launch");
   }
@@ -605,7 +609,9 @@ hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64
   unsigned long long* prefix = c.take<unsigned long long>((size_t)nq * sizeof(unsigned long long));
   uint32_t* remaining = c.take<uint32_t>((size_t)nq * sizeof(uint32_t));
 
-  e = timed("topk", s, [&] { return launch_topk_rows(sample, nq, p.S, p.S, k, ss, si, s); });
+  e = timed("topk", s, [&] {
+    return launch_topk_rows(sample, nq, p.S, p.S, k, ss, si, scratch, s);
+  });
   if (e != hipSuccess) return hip_fail(e, "top-k launch");
   e = launch_dense_init(ss, nq, k, theta, tie, count, n_queued, s);
   if (e != hipSuccess) return hip_fail(e, "dense init launch");

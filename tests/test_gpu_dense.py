@@ -1,7 +1,8 @@
 """GPU parity of dense_ip_topk (exact inner-product top-k over an fp16 store) against the oracle.
 
 The call has three regimes, each covered here:
-  * the store is no larger than the exact sample (every row is scored and selected directly);
+  * the store is no larger than the exact sample, or all its scores are few enough to be kept
+    (at most 2^26): every row is scored and selected directly;
   * the filter path: rows past the sample are kept only when they beat the sample's k-th score;
   * the exact fallback: a query whose candidate list overflows is queued on the device and its
     k-th key found by a radix select over rescans of the store, then its top-k collected; the
@@ -176,6 +177,93 @@ def test_dense_topk_replays_in_a_hip_graph_with_overflow():
         torch.cuda.synchronize()
         assert torch.equal(gs, ref_s) and torch.equal(gi, ref_i), f"replay {rep}"
     assert gi[0].tolist() == list(range(a0, a0 + k))
+
+
+@pytest.mark.parametrize("nq,n,dim,k,copies", [
+    (520, 140_000, 16, 50, 0),         # filtered scan with wide tiles
+    (64, 1_100_000, 8, 20, 0),         # ... with narrow ones
+    (520, 140_000, 16, 20, 3000),      # two overflowing lists: the exact fallback
+    (64, 1_100_000, 8, 20, 5000),
+])
+def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies):
+    # more than 2^26 scores: sample, filtered scan, merge, and the fallback for the overflowing lists
+    assert nq * n > 1 << 26 and n > SAMPLE_ROWS
+    Q, X = _rows(nq, dim, 51 + nq), _rows(n, dim, 52 + nq)
+    at = {0: SAMPLE_ROWS + 100, nq - 1: n - copies - 1}
+    if copies:
+        for q, a in at.items():
+            X[a:a + copies] = Q[q]
+    Qd, Xd = Q.to(DEV), X.to(DEV)
+    s, i = hpr.dense_ip_topk(Qd, Xd, k)
+    ws = hpr.dense_workspace(Qd, Xd, k)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        hpr.dense_ip_topk(Qd, Xd, k, ws=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        gs, gi = hpr.dense_ip_topk(Qd, Xd, k, ws=ws)
+    for rep in range(3):
+        gs.fill_(float("nan"))
+        g.replay()
+        hpr.dense_ip_topk(Qd[:3].contiguous(), Xd, 5)   # unrelated eager work
+        torch.cuda.synchronize()
+        assert torch.equal(gs, s) and torch.equal(gi, i), f"replay {rep}"
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    _check_structure(s, i, n, k)
+    pick = [0, 1, nq // 2, nq - 1]
+    O = oracle.dense_scores(_f16(Q[pick]), _f16(X))
+    for r, q in enumerate(pick):
+        if copies and q in at:  # bit-identical rows, the highest scores: the lowest indices
+            dup = O[r].max() - 1e-9
+            lowest = np.nonzero(O[r] >= dup)[0][:k]
+            assert i[q].tolist() == lowest.tolist()
+        else:
+            check_topk(s[q], i[q], O[r], k, rel=REL)
+
+
+def _exact_scores(kind, n, rng):
+    """Integers below 2^20 in magnitude whose order the select must reproduce, ties included."""
+    if kind == "normal":
+        v = np.round(rng.standard_normal(n) * 2e5)
+    elif kind == "ties":         # a few distinct scores, the k-th among hundreds of equals
+        v = np.round(rng.standard_normal(n) * 3) * 4096
+    elif kind == "negative":     # the winners are the smallest magnitudes
+        v = -np.abs(np.round(rng.standard_normal(n) * 2e5)) - 3
+    elif kind == "ascending":    # the winners are the row's last entries
+        v = np.arange(n) * (2 ** 20 - 1) // n
+    elif kind == "equal":
+        v = np.full(n, 77)
+    else:                        # one score far above a narrow crowd
+        v = rng.integers(500_000, 500_400, n)
+        v[n // 3] = 2 ** 20 - 1
+    return np.clip(v, -2 ** 20, 2 ** 20 - 1).astype(np.int64)
+
+
+@pytest.mark.parametrize("nq,n,k", [
+    (2, 64, 64), (2, 1025, 129), (2, 8192, 1000), (2, 8193, 1000),  # whole-row lists, then streams
+    (1, 59_999, 128), (1, 60_000, 129), (3, 60_001, 1), (2, 300_003, 1024),  # then slices
+    (64, 70_000, 10), (65, 70_000, 10),                               # ... of at most 64 rows
+])
+@pytest.mark.parametrize("kind", ["normal", "ties", "negative", "ascending", "equal", "outlier"])
+def test_dense_topk_select(nq, n, k, kind):
+    # scores of 20 bits, exact in fp32: the list must be exactly the sorted order (score desc,
+    # index asc), whatever the spread of the scores, on every path of the select
+    rng = np.random.default_rng(n + k)
+    v = _exact_scores(kind, n, rng)
+    X = np.zeros((n, 8), dtype=np.float16)
+    X[:, 0], X[:, 1] = v >> 10, v & 1023
+    Q = np.zeros((nq, 8), dtype=np.float16)
+    Q[:, 0], Q[:, 1] = 1.0, 2.0 ** -10
+    Q[1::2] *= -1  # the other queries rank by the negated scores
+    s, i = hpr.dense_ip_topk(torch.from_numpy(Q).to(DEV), torch.from_numpy(X).to(DEV), k)
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    for q in range(nq):
+        sign = -1 if q % 2 else 1
+        order = np.lexsort((np.arange(n), -sign * v))[:k]
+        assert np.array_equal(i[q], order), f"query {q}"
+        assert np.array_equal(s[q] * 1024, sign * v[order])
 
 
 def test_dense_topk_planted_rows_rank_first():
