@@ -25,20 +25,20 @@
 //      once when it is 0, so the call never synchronises with the host and is capturable in a
 //      HIP graph.
 //
-// GEMM tile: 256 queries x 256 rows per 8-wave workgroup (each wave 64 x 128 = 2 x 4 blocks of
-// v_mfma_f32_32x32x16_f16; 128 x 128 per wave at one wave per SIMD measured 20 % slower).  K
-// advances 64 halves per stage through two 64 KiB LDS buffers filled by direct-to-LDS buffer
-// loads (buffer_load_dwordx4 ... lds: a tile base in the resource, the stage's K offset as the
-// scalar offset, a 32-bit lane offset), each wave load covering 8 whole 128-byte row segments:
-// on this chip the direct-to-LDS path moves data at about twice the rate with whole cache lines
-// as with the half lines of 32-half stages, and the copy into LDS, not the MFMA, is what bounds
-// the loop (without it the same loop runs at the MFMA rate).  One barrier per stage, placed
-// before the stage's last k-step, whose MFMAs run while the next stage's first operands are
-// read.  In LDS the 16-byte chunk p of row r is stored at position p ^ ((r >> 2) & 3), which
-// keeps the operand reads free of bank conflicts.  Calls with at most 64 queries use a narrow
-// 64 x 256 tile (4 waves, two workgroups per CU, a 4-deep ring of 32-half stages): there the
-// row stream from HBM is the bound.  The filter epilogue compacts the passing entries per lane
-// in LDS and appends them with one round of list atomics per slot.
+// GEMM tile of many queries: 256 queries x 256 rows per 8-wave workgroup (each wave 64 x 128 = 2 x
+// 4 blocks of v_mfma_f32_32x32x16_f16; 128 x 128 per wave at one wave per SIMD measured 16-20 %
+// slower).  K advances 64 halves per stage through two 64 KiB LDS buffers filled by direct-to-LDS
+// buffer loads (buffer_load_dwordx4 ... lds: a tile base in the resource, the stage's K offset as
+// the scalar offset, a 32-bit lane offset), each wave load covering 8 whole 128-byte row segments:
+// on this chip the direct-to-LDS path moves data at about twice the rate with whole cache lines as
+// with the half lines of 32-half stages, and the copy into LDS, not the MFMA, is what bounds the
+// loop (without it the same loop runs at the MFMA rate).  One barrier per stage, placed before the
+// stage's last k-step, whose MFMAs run while the next stage's first operands are read.  In LDS the
+// 16-byte chunk p of row r is stored at position p ^ ((r >> 2) & 3), which keeps the operand reads
+// free of bank conflicts.  Calls of fewer queries or rows take smaller tiles (tile_of): there the
+// row stream from HBM, the padding queries or the idle CUs are the bound.  The filter epilogue
+// compacts the passing entries per lane in LDS and appends them with one round of list atomics per
+// slot.
 #include "common.h"
 #include "kernels.h"
 
@@ -48,7 +48,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// Workgroup tile geometry: TQ queries x 256 rows, WQ x WR waves, an NST-deep LDS ring of
+// Workgroup tile geometry: TQ queries x TR rows, WQ x WR waves, an NST-deep LDS ring of
 // K stages of KC halves each, holding the query tile then the row tile.
 //
 // LDS layout of a stage: 1 KiB blocks, one per 16-byte-per-lane wave load, each holding
@@ -56,10 +56,10 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 // [32 h, 32 h + 32) of the stage for the block's R rows as 64-byte rows; the 16-byte chunk p of
 // row r is stored at position p ^ ((r >> 2) & 3).  With KC = 64 one wave load reads 8 whole
 // 128-byte rows (full cache lines); with KC = 32, 16 half lines.
-template <int TQ, int WQ, int WR, int KC, int NST, int MIN_WG>
+template <int TQ, int TR, int WQ, int WR, int KC, int NST, int MIN_WG>
 struct GemmGeom {
   static constexpr int kTQ = TQ;                    // queries per workgroup tile
-  static constexpr int kTR = 256;                   // rows per workgroup tile
+  static constexpr int kTR = TR;                    // rows per workgroup tile
   static constexpr int kKC = KC;                    // halves of K per stage
   static constexpr int kKSteps = KC / 16;           // MFMA k-steps per stage
   static constexpr int kRowsPerBlock = 512 / KC;    // rows per 1 KiB block
@@ -82,13 +82,20 @@ struct GemmGeom {
   static_assert(kQTileBytes % 1024 == 0, "no wave load straddles the two tiles");
   static_assert(32 * kBQ <= 64, "a wave's queries fit one lane each");
 };
-// Many queries: 256 x 256 tiles, 8 waves of 64 x 128 (2 x 4 blocks), one workgroup per CU; two
-// 64 KiB stages of 64 halves.
-using GeomWide = GemmGeom<256, 4, 2, 64, 2, 1>;
-// At most 64 queries: 64 x 256 tiles, 4 waves of 64 x 64 (2 x 2 blocks), two workgroups per CU
-// (2 x 80 KiB of LDS), a 4-deep ring of 20 KiB stages.  The row stream is the bound there; the
-// wide tile would multiply up to 192 padding queries per row.
-using GeomNarrow = GemmGeom<64, 1, 4, 32, 4, 2>;
+// The tiles, from the largest; tile_of says which call takes which.
+//   wide    256 x 256, 8 waves of 64 x 128 (2 x 4 blocks), one workgroup per CU (two 64 KiB stages)
+//   mid     128 x 128, 4 waves of 64 x 64, two workgroups per CU (two 32 KiB stages)
+//   narrow  64 x 128, 4 waves of 64 x 32, three workgroups per CU (two 24 KiB stages)
+//   skinny  32 x 128, 4 waves of 32 x 32, two workgroups per CU (a ring of four 20 KiB stages)
+//   short   32 x 64, 2 waves of 32 x 32, three workgroups per CU (a ring of four 12 KiB stages)
+//   long    64 x 256, 4 waves of 64 x 64, two workgroups per CU (a ring of four 20 KiB stages of 32
+//           halves): the filtered scan's at 33 to 64 queries, and the fallback's
+using GeomWide = GemmGeom<256, 256, 4, 2, 64, 2, 1>;
+using GeomMid = GemmGeom<128, 128, 2, 2, 64, 2, 2>;
+using GeomNarrow = GemmGeom<64, 128, 1, 4, 64, 2, 3>;
+using GeomSkinny = GemmGeom<32, 128, 1, 4, 64, 4, 2>;
+using GeomShort = GemmGeom<32, 64, 1, 2, 64, 4, 3>;
+using GeomLong = GemmGeom<64, 256, 1, 4, 32, 4, 2>;
 
 // 16 zero bytes in global memory: the source of the K-tail chunks past `dim`.
 __device__ __attribute__((aligned(16))) const uint32_t kZero16[4] = {0u, 0u, 0u, 0u};
@@ -133,7 +140,7 @@ struct GemmArgs {
 
 enum GemmMode { kStore = 0, kFilter = 1, kHist = 2 };
 
-// One 256-row tile of X against query tile qt (queries [qt kTQ, qt kTQ + kTQ) of the nqa of
+// One row tile of X against query tile qt (queries [qt kTQ, qt kTQ + kTQ) of the nqa of
 // the launch).
 template <typename G, int MODE>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int nqa, int qt, int rt,
@@ -311,12 +318,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int nqa, int qt, in
       mfma(f1);
     }
   } else {
-    // Software pipeline over a ring of 32-half stages.  Every iteration issues exactly one
+    // Software pipeline over a ring of stages.  Every iteration issues exactly one
     // stage of loads (past the last stage, zeros into a buffer nobody reads again), so "stage
     // kk+1 has landed" is always "at most kStages - 3 stages of this wave's loads are still in
     // flight".
-    static_assert(kKSteps == 2 && kStages >= 3 && (kStages - 2) * kLoadsPerWave <= 63,
-                  "two k-steps per stage; vmcnt range");
+    static_assert(kStages >= 3 && (kStages - 2) * kLoadsPerWave <= 63, "vmcnt range");
 #pragma unroll
     for (int s = 0; s < kStages - 1; ++s) issue(s, s);
     // stage 0 landed (this wave): at most the kStages - 2 later stages still in flight
@@ -327,6 +333,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int nqa, int qt, in
     for (int kk = 0; kk < nk; ++kk) {
       read_frags(kk, 1, f1);
       mfma(f0);
+      if constexpr (kKSteps == 4) {
+        read_frags(kk, 2, f0);
+        mfma(f1);
+        read_frags(kk, 3, f1);
+        mfma(f0);
+      }
       // Stage kk+1 lands everywhere, and every wave's reads of stage kk-1 are complete (this
       // wave's LDS reads drain before the barrier), so that stage's buffer
       // ((kk + kStages - 1) % kStages) can take stage kk + kStages - 1.
@@ -756,13 +768,64 @@ hipError_t launch_gemm_t(const GemmArgs& a, unsigned blocks, hipStream_t stream)
   return hipGetLastError();
 }
 
+// One launch, or, where a grid would reach 2^32 threads, one per run of row tiles.
 template <typename G, int MODE>
-hipError_t launch_gemm_grid(GemmArgs a, int64_t n_rt, hipStream_t stream) {
-  a.n_qt = (a.nqa + G::kTQ - 1) / G::kTQ;
-  if (n_rt < 1 || n_rt > 0x7fffffffLL || (int64_t)a.n_qt * n_rt > 0xffffffffLL)
-    return hipErrorInvalidValue;
-  a.n_rt = (int)n_rt;
-  return launch_gemm_t<G, MODE, false>(a, (unsigned)((int64_t)a.n_qt * n_rt), stream);
+hipError_t launch_gemm_grid(GemmArgs a, hipStream_t stream) {
+  a.n_qt = (int)(((int64_t)a.nqa + G::kTQ - 1) / G::kTQ);
+  const int64_t most = (int64_t)0x7fffffff / G::kThreads / a.n_qt * G::kTR;  // rows per launch
+  if (most < G::kTR) return hipErrorInvalidValue;
+  const int64_t r1 = a.r1;
+  hipError_t e = hipSuccess;
+  while (e == hipSuccess && a.r0 < r1) {
+    a.r1 = r1 - a.r0 < most ? r1 : a.r0 + most;
+    a.n_rt = (int)((a.r1 - a.r0 + G::kTR - 1) / G::kTR);
+    e = launch_gemm_t<G, MODE, false>(a, (unsigned)(a.n_qt * a.n_rt), stream);
+    if (MODE == kStore) a.scores += a.r1 - a.r0;
+    a.r0 = a.r1;
+  }
+  return e;
+}
+
+enum GemmTile { kWide, kMid, kNarrow, kSkinny, kShort };
+
+// The largest tile whose grid still fills the chip.  A larger tile reads the operands fewer times
+// (4096 queries x 131,072 rows x 4096: wide 3.84 ms, mid 4.88, narrow 6.05, skinny 10.0), a tile
+// walks K alone on its share of a CU (dim 4096: short 20 us, skinny 23, narrow 42, mid 47, wide 73),
+// and what a tile holds beyond the call's queries is multiplied for nothing.  Where the lines lie
+// (us, dim 768 unless stated):
+//   wide from 144 of them: 1000 x 10,000 (160 tiles) wide 29, mid 35, narrow 31; 200 x 25,000 (98)
+//     28, 22, 28; up to 128 queries half of it is padding: 128 x 400,000 x 4096 wide 927, mid 749
+//   mid from 384: 100 x 50,000 (391) mid 22, narrow 28; 100 x 25,000 (196) 19, 16; up to 64
+//     queries 64 x 1,000,000 x 1024 mid 508, narrow 453
+//   narrow from 300: 200 x 10,000 (316) narrow 16, skinny 18; 48 x 25,000 (196) 15, 14; up to 32
+//     queries 16 x 1,000,000 x 1024 narrow 397, skinny 395
+//   skinny from 192: 48 x 25,000 (392) skinny 14, short 16; 16 x 10,000 (79) 9.1, 8.5.  Many rounds
+//     of long rows stream best through short tiles: 1 x 1,000,000 x 4096 short 1307, skinny 1334;
+//     at dim 1024 skinny 395, short 400
+int tile_of(int64_t nq, int64_t rows, int dim) {
+  auto grid = [&](int64_t tq, int64_t tr) {
+    return ((nq + tq - 1) / tq) * ((rows + tr - 1) / tr);
+  };
+  if (nq > 128 && grid(256, 256) >= 144) return kWide;
+  if (nq > 64 && grid(128, 128) >= 384) return kMid;
+  if (nq > 32 && grid(64, 128) >= 300) return kNarrow;
+  if (nq <= 32 && dim >= 2048 && rows >= 65536 * 3) return kShort;
+  return grid(32, 128) >= 192 ? kSkinny : kShort;
+}
+
+template <int MODE>
+hipError_t launch_gemm_mode(int tile, const GemmArgs& a, hipStream_t stream) {
+  switch (tile) {
+    case kWide: return launch_gemm_grid<GeomWide, MODE>(a, stream);
+    case kMid: return launch_gemm_grid<GeomMid, MODE>(a, stream);
+    case kNarrow:
+      if constexpr (MODE == kStore) return launch_gemm_grid<GeomNarrow, MODE>(a, stream);
+      // twice the rows per filter epilogue: 60 x 3,000,000 x 384 in 576 us against 625 (60 x
+      // 1,500,000 x 1024: 573 against 583)
+      return launch_gemm_grid<GeomLong, MODE>(a, stream);
+    case kSkinny: return launch_gemm_grid<GeomSkinny, MODE>(a, stream);
+    default: return launch_gemm_grid<GeomShort, MODE>(a, stream);
+  }
 }
 
 }  // namespace
@@ -789,25 +852,20 @@ hipError_t launch_dense_gemm(const DenseGemm& g, int n_cu, hipStream_t stream) {
   a.hist = g.hist;
   a.prefix = g.prefix;
   a.shift = g.shift;
-  const int64_t n_rt = (g.r1 - g.r0 + 255) / 256;
-  if (g.m_dev) {  // persistent narrow-tile grid over the *m_dev queued queries
+  if (g.m_dev) {  // persistent grid over the *m_dev queued queries
+    const int64_t n_rt = (g.r1 - g.r0 + GeomLong::kTR - 1) / GeomLong::kTR;
     if (n_rt > 0x7fffffffLL || !g.qmap) return hipErrorInvalidValue;
     a.n_rt = (int)n_rt;
-    const unsigned blocks = (unsigned)((n_cu > 0 ? n_cu : 256) * GeomNarrow::kMinWG);
-    if (g.mode == kHist) return launch_gemm_t<GeomNarrow, kHist, true>(a, blocks, stream);
-    if (g.mode == kFilter) return launch_gemm_t<GeomNarrow, kFilter, true>(a, blocks, stream);
+    const unsigned blocks = (unsigned)((n_cu > 0 ? n_cu : 256) * GeomLong::kMinWG);
+    if (g.mode == kHist) return launch_gemm_t<GeomLong, kHist, true>(a, blocks, stream);
+    if (g.mode == kFilter) return launch_gemm_t<GeomLong, kFilter, true>(a, blocks, stream);
     return hipErrorInvalidValue;
   }
-  const bool narrow = g.nqa <= GeomNarrow::kTQ;
+  const int tile = tile_of(g.nqa, g.r1 - g.r0, g.dim);
   switch (g.mode) {
-    case kStore:
-      return narrow ? launch_gemm_grid<GeomNarrow, kStore>(a, n_rt, stream)
-                    : launch_gemm_grid<GeomWide, kStore>(a, n_rt, stream);
-    case kFilter:
-      return narrow ? launch_gemm_grid<GeomNarrow, kFilter>(a, n_rt, stream)
-                    : launch_gemm_grid<GeomWide, kFilter>(a, n_rt, stream);
-    default:
-      return hipErrorInvalidValue;
+    case kStore: return launch_gemm_mode<kStore>(tile, a, stream);
+    case kFilter: return launch_gemm_mode<kFilter>(tile, a, stream);
+    default: return hipErrorInvalidValue;
   }
 }
 

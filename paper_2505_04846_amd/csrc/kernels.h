@@ -150,7 +150,7 @@ inline DensePlan dense_plan(int nq, int64_t n, int k) {
 //                prefix[g], bin (key >> shift) & 255 of hist[q] is incremented
 //                (key = score key << 32 | ~row).
 // With m_dev the launch is a persistent grid over the *m_dev queries (read on the device; qmap
-// required; nqa unused), narrow tiles, filter or histogram mode.
+// required; nqa unused), filter or histogram mode.
 struct DenseGemm {
   int mode;
   const uint16_t* q;

@@ -223,6 +223,30 @@ def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies):
             check_topk(s[q], i[q], O[r], k, rel=REL)
 
 
+@pytest.mark.parametrize("nq,n,dim,k", [
+    (129, 18_400, 72, 10), (256, 18_177, 64, 10),   # 144 wide tiles, the last one ragged
+    (257, 12_000, 40, 10), (128, 49_100, 24, 10),    # one fewer; 384 mid tiles
+    (65, 49_025, 136, 10), (65, 48_900, 136, 10),
+    (33, 38_300, 200, 10), (64, 38_280, 8, 10),       # 300 narrow tiles and one fewer
+    (32, 24_500, 72, 10), (1, 24_449, 1032, 10), (33, 12_200, 128, 10),  # 192 skinny tiles
+    (31, 24_448, 72, 10), (1, 65, 4096, 10),          # short ones
+    (2, 196_608, 2048, 5), (32, 196_607, 64, 5),      # many rounds of long rows: short
+])
+def test_dense_topk_tile_choice(nq, n, dim, k):
+    # both sides of every line between the GEMM's tiles, ragged in queries, rows and K
+    Q, X = _rows(nq, dim, 61 + n), _rows(n, dim, 62 + n)
+    X[n - 1], X[0] = Q[nq - 1], Q[0]  # the edges of the tiles hold winners
+    s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    _check_structure(s, i, n, k)
+    assert i[nq - 1, 0] == n - 1 or nq == 1
+    assert 0 in i[0]
+    pick = sorted({0, nq // 2, nq - 1})
+    O = oracle.dense_scores(_f16(Q[pick]), _f16(X))
+    for r, q in enumerate(pick):
+        check_topk(s[q], i[q], O[r], k, rel=REL)
+
+
 def _exact_scores(kind, n, rng):
     """Integers below 2^20 in magnitude whose order the select must reproduce, ties included."""
     if kind == "normal":
