@@ -37,7 +37,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 / fp16 MFMA
 PEAK_HBM_GBS = 8000.0
 COPY_CALIBRATION_BYTES = 256 << 20  # bytes read (and written) by each calibration copy
 CPU_SAMPLE_SECONDS = 10.0  # the oracle sample is repeated for at least this long
-KERNELS = ("partition", "maxsim", "maxsim_argmax", "topk", "infonce", "pool", "contrastive",
+KERNELS = ("partition", "maxsim", "maxsim_argmax", "topk", "infonce", "infonce_pool", "contrastive",
            "grad_q", "grad_d", "dense_sample", "dense_scan", "dense_merge", "dense_fallback",
            "semantic_chunk", "retrieval_metrics")
 

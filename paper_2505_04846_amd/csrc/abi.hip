@@ -263,14 +263,15 @@ hpr_status run_loss(const uint16_t* q, int32_t nq, int32_t lq, const uint16_t* d
                   s);
   if (st != HPR_OK) return st;
   const float w = total ? 0.5f : 1.0f;
-  hipError_t e = timed("infonce", s, [&] {
-    return launch_infonce(S, nq, n_docs, pos_idx, logit_scale, w, G, terms, total ? loss + 1 : loss,
-                          scores, ctrl, s);
-  });
-  if (e != hipSuccess) return hip_fail(e, "infonce launch");
+  hipError_t e = hipSuccess;
   float* dqc = nullptr;
   float* ddc = nullptr;
-  if (total) {
+  if (!total) {
+    e = timed("infonce", s, [&] {
+      return launch_infonce(S, nq, n_docs, pos_idx, logit_scale, w, G, terms, loss, scores, ctrl, s);
+    });
+    if (e != hipSuccess) return hip_fail(e, "infonce launch");
+  } else {
     float* Uq = c.take<float>((size_t)nq * dim * sizeof(float));
     float* Ud = c.take<float>((size_t)n_docs * dim * sizeof(float));
     float* gsc_q = c.take<float>((size_t)nq * sizeof(float));
@@ -279,10 +280,11 @@ hpr_status run_loss(const uint16_t* q, int32_t nq, int32_t lq, const uint16_t* d
     float* terms_c = c.take<float>((size_t)nq * sizeof(float));
     dqc = c.take<float>((size_t)nq * dim * sizeof(float));
     ddc = c.take<float>((size_t)n_docs * dim * sizeof(float));
-    e = timed("pool", s, [&] {
-      return launch_pool(q, nq, lq, d_tok, d_off, n_docs, n_tok, dim, Uq, Ud, gsc_q, gsc_d, s);
+    e = timed("infonce_pool", s, [&] {
+      return launch_infonce_pool(S, pos_idx, logit_scale, w, G, terms, loss + 1, ctrl, q, nq, lq,
+                                 d_tok, d_off, n_docs, n_tok, dim, Uq, Ud, gsc_q, gsc_d, s);
     });
-    if (e != hipSuccess) return hip_fail(e, "pooling launch");
+    if (e != hipSuccess) return hip_fail(e, "InfoNCE and pooling launch");
     e = timed("contrastive", s, [&] {
       return launch_contrastive(Uq, gsc_q, Ud, gsc_d, nq, n_docs, dim, pos_idx, tau, w, w, dC,
                                 terms_c, dqc, ddc, loss, ctrl, s);
