@@ -113,14 +113,30 @@ def _check(status):
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _launch(fn, device, *args):
+    """fn(*args, stream) with `device` current and its current stream last; raises on a status.
+    Entering torch's device guard costs about as much as a kernel launch, so only a call for
+    another device than the current one does."""
+    if torch.cuda.current_device() == device.index:
+        status = fn(*args, _stream(device))
+    else:
+        with torch.cuda.device(device):
+            status = fn(*args, _stream(device))
+    if status != 0:
+        _check(status)
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _need(t, name, dtype, ndim, device=None):
+    if (isinstance(t, torch.Tensor) and t.dtype == dtype and t.dim() == ndim and t.is_cuda
+            and (device is None or t.device == device) and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -161,9 +177,8 @@ def maxsim_score(Q, D, off, ws=None):
     need = L.maxsim_score_workspace_size(nq, lq, n_docs, n_tok, dim)
     ws = ws if ws is not None and ws.numel() >= need else _workspace(need, dev)
     scores = torch.empty((nq, n_docs), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.maxsim_score(_ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim,
-                              _ptr(scores), _ptr(ws), ws.numel(), _stream(dev)))
+    _launch(L.maxsim_score, dev, _ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim,
+            _ptr(scores), _ptr(ws), ws.numel())
     return scores
 
 
@@ -176,9 +191,8 @@ def maxsim_score_noalloc(Q, D, off, out=None):
     _need(scores, "out", torch.float32, 2, dev)
     if tuple(scores.shape) != (nq, n_docs):
         raise ValueError(f"out must be [{nq}, {n_docs}]")
-    with torch.cuda.device(dev):
-        _check(lib().maxsim_score_noalloc(_ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim,
-                                          _ptr(scores), _stream(dev)))
+    _launch(lib().maxsim_score_noalloc, dev, _ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok,
+            dim, _ptr(scores))
     return scores
 
 
@@ -189,9 +203,8 @@ def maxsim_topk(Q, D, off, k, ws=None):
     ws = ws if ws is not None and ws.numel() >= need else _workspace(need, dev)
     out_s = torch.empty((nq, k), dtype=torch.float32, device=dev)
     out_i = torch.empty((nq, k), dtype=torch.int64, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.maxsim_topk(_ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim, int(k),
-                             _ptr(out_s), _ptr(out_i), _ptr(ws), ws.numel(), _stream(dev)))
+    _launch(L.maxsim_topk, dev, _ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim, int(k),
+            _ptr(out_s), _ptr(out_i), _ptr(ws), ws.numel())
     return out_s, out_i
 
 
@@ -226,11 +239,9 @@ def coltrast_loss_fwd_bwd(Q, D, off, pos, logit_scale, need_dq=True, need_dd=Tru
     scores = out.get("scores") if return_scores else None
     if return_scores and scores is None:
         scores = torch.empty((nq, n_docs), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.coltrast_loss_fwd_bwd(_ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim,
-                                       _ptr(pos), float(logit_scale), _ptr(loss), _ptr(dq),
-                                       _ptr(dd), _ptr(scores), _ptr(ws), ws.numel(),
-                                       _stream(dev)))
+    _launch(L.coltrast_loss_fwd_bwd, dev, _ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok, dim,
+            _ptr(pos), float(logit_scale), _ptr(loss), _ptr(dq), _ptr(dd), _ptr(scores), _ptr(ws),
+            ws.numel())
     return {"loss": loss, "dq": dq, "dd": dd, "scores": scores}
 
 
@@ -262,18 +273,15 @@ def coltrast_total_loss_fwd_bwd(Q, D, off, pos, logit_scale, temperature, need_d
     dd = out.get("dd") if need_dd else None
     if need_dd and dd is None:
         dd = torch.empty(D.shape, dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.coltrast_total_loss_fwd_bwd(_ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok,
-                                             dim, _ptr(pos), float(logit_scale),
-                                             float(temperature), _ptr(loss), _ptr(dq), _ptr(dd),
-                                             _ptr(ws), ws.numel(), _stream(dev)))
+    _launch(L.coltrast_total_loss_fwd_bwd, dev, _ptr(Q), nq, lq, _ptr(D), _ptr(off), n_docs, n_tok,
+            dim, _ptr(pos), float(logit_scale), float(temperature), _ptr(loss), _ptr(dq), _ptr(dd),
+            _ptr(ws), ws.numel())
     return {"loss": loss, "dq": dq, "dd": dd}
 
 
 def scale_(x, scale):
     """x *= scale in place (x fp32 contiguous CUDA tensor, scale a 1-element fp32 CUDA tensor)."""
-    with torch.cuda.device(x.device):
-        _check(lib().hpr_scale_f32(_ptr(x), x.numel(), _ptr(scale), _stream(x.device)))
+    _launch(lib().hpr_scale_f32, x.device, _ptr(x), x.numel(), _ptr(scale))
     return x
 
 
@@ -285,9 +293,8 @@ def _scaled_grads(dq, dd, scale):
     out = [None if t is None else torch.empty(t.shape, dtype=torch.bfloat16, device=device)
            for t in src]
     q, d = [0 if t is None else t.numel() for t in src]
-    with torch.cuda.device(device):
-        _check(lib().hpr_scale_grads_bf16(_ptr(src[0]), q, _ptr(out[0]), _ptr(src[1]), d,
-                                          _ptr(out[1]), _ptr(scale), _stream(device)))
+    _launch(lib().hpr_scale_grads_bf16, device, _ptr(src[0]), q, _ptr(out[0]), _ptr(src[1]), d,
+            _ptr(out[1]), _ptr(scale))
     return out
 
 
@@ -304,7 +311,7 @@ class _ColTrastLI(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_out):
         saved = list(ctx.saved_tensors)
-        g = grad_out.reshape(1).to(torch.float32).contiguous()
+        g = grad_out.to(torch.float32)  # a scalar: 0-dimensional
         dq = saved.pop(0) if ctx.has[0] else None
         dd = saved.pop(0) if ctx.has[1] else None
         # the saved gradients stay as the forward left them, so a second backward over a retained
@@ -353,9 +360,8 @@ def dense_ip_topk(Q, X, k, ws=None):
     ws = ws if ws is not None and ws.numel() >= need else _workspace(need, dev)
     out_s = torch.empty((nq, k), dtype=torch.float32, device=dev)
     out_i = torch.empty((nq, k), dtype=torch.int64, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.dense_ip_topk(_ptr(Q), nq, _ptr(X), n, dim, int(k), _ptr(out_s), _ptr(out_i),
-                               _ptr(ws), ws.numel(), _stream(dev)))
+    _launch(L.dense_ip_topk, dev, _ptr(Q), nq, _ptr(X), n, dim, int(k), _ptr(out_s), _ptr(out_i),
+            _ptr(ws), ws.numel())
     return out_s, out_i
 
 
@@ -388,10 +394,8 @@ def semantic_chunk(E, paper_off, threshold, return_cos=False, ws=None, out=None)
     cos = out.get("cos") if return_cos else None
     if return_cos and cos is None:
         cos = torch.empty(n, dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(L.semantic_chunk(_ptr(E), n, dim, _ptr(paper_off), n_papers, float(threshold),
-                                _ptr(cos), _ptr(seg), _ptr(n_seg), _ptr(ws), ws.numel(),
-                                _stream(dev)))
+    _launch(L.semantic_chunk, dev, _ptr(E), n, dim, _ptr(paper_off), n_papers, float(threshold),
+            _ptr(cos), _ptr(seg), _ptr(n_seg), _ptr(ws), ws.numel())
     return {"seg": seg, "n_segments": n_seg, "cos": cos}
 
 
@@ -411,9 +415,8 @@ def retrieval_metrics(idx, positive, k=None):
         raise ValueError("positive must hold one index per query")
     metrics = torch.empty(2, dtype=torch.float64, device=dev)
     ranks = torch.empty(nq, dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib().retrieval_metrics(_ptr(idx), nq, ld, k, _ptr(positive), _ptr(ranks),
-                                       _ptr(metrics), _stream(dev)))
+    _launch(lib().retrieval_metrics, dev, _ptr(idx), nq, ld, k, _ptr(positive), _ptr(ranks),
+            _ptr(metrics))
     return {"metrics": metrics, "ranks": ranks}
 
 

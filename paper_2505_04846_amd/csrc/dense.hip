@@ -760,9 +760,11 @@ namespace {
 template <typename G, int MODE, bool PERSIST>
 hipError_t launch_gemm_t(const GemmArgs& a, unsigned blocks, hipStream_t stream) {
   const int lds = G::kStages * G::kStageBytes;
-  const void* fn = (const void*)dense_gemm_kernel<G, MODE, PERSIST>;
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e != hipSuccess) return e;
+  if (lds > 65536) {  // beyond the default dynamic LDS limit
+    const void* fn = (const void*)dense_gemm_kernel<G, MODE, PERSIST>;
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((dense_gemm_kernel<G, MODE, PERSIST>), dim3(blocks), dim3(G::kThreads), lds,
                      stream, a);
   return hipGetLastError();
