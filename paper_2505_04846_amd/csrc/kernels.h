@@ -22,7 +22,8 @@ struct MaxsimPlan {
   int qpw;         // queries per wave
   int n_qgroups;   // workgroups along the query axis
   int n_ranges;    // document ranges (workgroups along the document axis)
-  bool own_ranges; // the workgroups find their ranges themselves (no range table)
+  bool own_ranges; // the workgroups find their ranges themselves (no range table) ...
+  bool by_count;   // ... as equal numbers of documents
   bool persist;    // score kernel: one range per XCD, one launch of one resident round per pass
                    // of query groups
   int64_t grid;    // workgroups per launch

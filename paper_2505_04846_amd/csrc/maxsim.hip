@@ -132,9 +132,9 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
     d_begin = __builtin_amdgcn_readfirstlane((int)part[rng]);
     d_end = __builtin_amdgcn_readfirstlane((int)part[rng + 1]);
   } else {
-    const int first = range_first_doc(off, a.n_docs, a.n_tok, a.n_ranges, rng, lane);
-    d_begin = __builtin_amdgcn_readlane(first, 0);
-    d_end = __builtin_amdgcn_readlane(first, 32);
+    const DocRange own = own_range(a, off, rng, lane);
+    d_begin = own.first;
+    d_end = own.last;
   }
   if (d_begin >= d_end || qg >= a.n_qgroups) return;  // uniform for the whole workgroup
   const int qwg = qg * WPW * a.qpw;  // first query of the workgroup
@@ -627,6 +627,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
   // One round of workgroups finds its ranges itself, which saves the partition launch; later
   // rounds would each pay the search's latency again.
   p->own_ranges = argmax || p->grid <= round;
+  p->by_count = p->own_ranges && n_docs < 2 * (int64_t)p->n_ranges;
   auto fits = [](int64_t groups, int slots) {
     return slots > 0 && groups >= 2 * slots && (groups % slots == 0 || groups >= 8 * slots);
   };
@@ -634,7 +635,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     const int slots = n_cu / 8 * occ;  // resident workgroups per XCD
     if (fits(p->n_qgroups, slots)) {
       p->persist = true;
-      p->own_ranges = false;
+      p->own_ranges = p->by_count = false;
       p->n_ranges = 8;
       p->grid = (int64_t)8 * slots;
       if (p->ks == 8 && p->nb == 4 && occ % 2 == 0) {
@@ -688,6 +689,7 @@ hipError_t launch_maxsim(const MaxsimPlan& plan, int pass, const uint16_t* q, in
   args.dim = dim;
   args.n_qgroups = plan.n_qgroups;
   args.n_ranges = plan.n_ranges;
+  args.by_count = plan.by_count ? 1 : 0;
   args.persist = plan.persist ? 1 : 0;
   args.qg_base = plan.persist ? pass * (int)(plan.grid / plan.n_ranges) : 0;
   return launch_variant(plan, args, amax != nullptr, stream);

@@ -125,9 +125,8 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
   // (the query operands are waited for together with the first stage's tiles, below)
 
   // ---- this workgroup's documents: found while the query loads are in flight
-  const int first = range_first_doc(off, a.n_docs, a.n_tok, a.n_ranges, rng, lane);
-  const int d_begin = __builtin_amdgcn_readlane(first, 0);
-  const int d_end = __builtin_amdgcn_readlane(first, 32);
+  const DocRange own = own_range(a, off, rng, lane);
+  const int d_begin = own.first, d_end = own.last;
   if (d_begin >= d_end) return;  // uniform for the whole workgroup
 
   const int n_tok = (int)a.n_tok;

@@ -24,6 +24,7 @@ struct MaxsimArgs {
   int nq, lq, lqp, qpw, dim, n_qgroups, n_ranges, n_ctrl;
   int persist;          // score kernel: persistent grid (see maxsim_kernel) ...
   int qg_base;          // ... and the first query group of the launch
+  int by_count;         // own ranges hold equal numbers of documents (see own_range)
 };
 
 // Position of tile `t` of the current document stream; uniform across the workgroup.  Token
@@ -79,6 +80,22 @@ __device__ __forceinline__ int range_first_doc(const int64_t* __restrict__ off, 
     }
   }
   return (int)lo;
+}
+
+// The documents [first, last) of range r, found by the workgroup itself.  By count (plan.by_count:
+// fewer than two documents a range): no balance of tokens is to be had from whole documents, and
+// equal numbers of them need no search.  Otherwise by tokens.
+struct DocRange {
+  int first, last;
+};
+__device__ __forceinline__ DocRange own_range(const MaxsimArgs& a, const int64_t* __restrict__ off,
+                                              int r, int lane) {
+  if (a.by_count) {
+    const uint32_t n = (uint32_t)a.n_docs, R = (uint32_t)a.n_ranges;  // n < 2 R <= 2^17
+    return {(int)(n / R * r + n % R * r / R), (int)(n / R * (r + 1) + n % R * (r + 1) / R)};
+  }
+  const int first = range_first_doc(off, a.n_docs, a.n_tok, a.n_ranges, r, lane);
+  return {__builtin_amdgcn_readlane(first, 0), __builtin_amdgcn_readlane(first, 32)};
 }
 
 // Argmax keys ("tile keys") of one 32x32 tile column: the lane's 16 values v_r (r = 0..15,
