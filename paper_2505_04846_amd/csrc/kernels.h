@@ -18,7 +18,8 @@ struct MaxsimPlan {
   int ks;          // k-steps of 16 (dim <= 16 * ks)
   int nb;          // 32-slot query blocks per wave
   int wpw;         // waves per workgroup
-  int lqp;         // query slots per query (lq rounded up to 32)
+  int lqp;         // query slots per query: lq rounded up to 32, or max(lq, 16) when packed
+  bool packed;     // queries follow one another in the slots, across blocks of 32
   int qpw;         // queries per wave
   int n_qgroups;   // workgroups along the query axis
   int n_ranges;    // document ranges (workgroups along the document axis)

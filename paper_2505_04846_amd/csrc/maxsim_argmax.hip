@@ -68,20 +68,23 @@ __device__ __forceinline__ int opaque(int v) {
   return r;
 }
 
-template <int KS, int NB, int WPW, bool DIRECT>
+template <int KS, int NB, int WPW, bool DIRECT, bool PACKED>
 __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
     MaxsimArgs a, const int64_t* __restrict__ off) {
   using G = ArgGeom<KS, DIRECT>;
   static_assert(!DIRECT || G::kTps == WPW, "direct staging: one tile per wave");
   // two workgroups per CU (what the plan assumes for every variant): two stages and the ring
-  static_assert(2 * (2 * G::kStageB + 3 * G::kTps * (WPW * NB * 4 + WPW * NB * 32 * 2)) <=
+  static_assert(2 * (2 * G::kStageB + 3 * G::kTps * (WPW * NB * 2 * 4 + WPW * NB * 32 * 2) +
+                     WPW * NB * 32 * 4) <=
                     160 * 1024,
                 "LDS of two resident workgroups");
   constexpr int kThreads = 64 * WPW;
   constexpr int kSlotsWG = WPW * NB * 32;
   constexpr int kTps = G::kTps;
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][G::kStageB];
-  __shared__ float res_score[3][kTps][kSlotsWG / 32];
+  constexpr int kQueries = kSlotsWG / (PACKED ? 16 : 32);  // at most, per workgroup
+  __shared__ float res_score[3][kTps][kQueries];
+  __shared__ float slot_max[PACKED ? WPW : 1][PACKED ? NB * 32 : 1];  // each wave's slot maxima
   __shared__ uint16_t res_amax[3][kTps][kSlotsWG];
 
   const int tid = threadIdx.x;
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
   bf16x8 bq[NB][KS];
   int slot_row[NB];
   uint32_t my_blocks = 0;
-  const int lqb = a.lqp >> 5;
+  const int lqb = (a.lq + 31) >> 5;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int slot = b * 32 + col;
@@ -332,6 +335,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
     }
     if (p.last) {
       float qs = 0.f;
+      float ms[PACKED ? NB : 1];
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         // the two half-waves (rows 0-15 and 16-31 of the tile column) meet through
@@ -353,11 +357,19 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
         if (half == 0 && slot_row[b] >= 0)
           res_amax[0][0][opaque(slot_row[b]) + (p.rb * kTps + p.j) * kSlotsWG] = (uint16_t)x;
         bk[b] = INT32_MIN;
-        const float v = half32_sum(slot_row[b] >= 0 ? m : 0.f);
-        if ((my_blocks >> b) & 1u) qs += v;
+        if constexpr (PACKED) {
+          ms[b] = m;
+        } else {
+          const float v = half32_sum(slot_row[b] >= 0 ? m : 0.f);
+          if ((my_blocks >> b) & 1u) qs += v;
+        }
       }
-      if (lane < a.qpw)
-        res_score[0][0][opaque(wave * a.qpw + lane) + (p.rb * kTps + p.j) * (kSlotsWG / 32)] = qs;
+      if constexpr (PACKED)
+        packed_sums<NB>(a, ms, slot_max[wave], lane, [&](int ql, float s) {
+          res_score[p.rb][p.j][wave * a.qpw + ql] = s;
+        });
+      else if (lane < a.qpw)
+        res_score[0][0][opaque(wave * a.qpw + lane) + (p.rb * kTps + p.j) * kQueries] = qs;
     }
   };
   // One pipelined step: the MFMAs of tile j (stage buffer `buf`) into X and, when HAS_Y, the
@@ -411,7 +423,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
       if (tid < n_wg_q)
         reinterpret_cast<uint32_t*>(a.scores)[(int64_t)(qwg + tid) * a.n_docs + d] =
             lng ? 0x7fc00000u
-                : __float_as_uint(res_score[0][0][opaque(tid) + slot * (kSlotsWG / 32)]);
+                : __float_as_uint(res_score[0][0][opaque(tid) + slot * kQueries]);
       uint16_t* dst = a.amax + (int64_t)d * n_entries + (int64_t)qwg * a.lq;
       for (int e = tid; e < n_wg_e; e += kThreads)
         dst[e] = res_amax[0][0][opaque(e) + slot * kSlotsWG];
@@ -502,9 +514,13 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
 
 template <int KS, int NB, int WPW, bool DIRECT = false>
 hipError_t launch_argmax_t(const MaxsimPlan& plan, const MaxsimArgs& args, hipStream_t stream) {
-  const int64_t blocks = (int64_t)plan.n_qgroups * plan.n_ranges;
-  hipLaunchKernelGGL((maxsim_argmax_kernel<KS, NB, WPW, DIRECT>), dim3((unsigned)blocks),
-                     dim3(64 * WPW), 0, stream, args, args.off);
+  const dim3 grid((unsigned)((int64_t)plan.n_qgroups * plan.n_ranges)), block(64 * WPW);
+  if (plan.packed)
+    hipLaunchKernelGGL((maxsim_argmax_kernel<KS, NB, WPW, DIRECT, true>), grid, block, 0, stream,
+                       args, args.off);
+  else
+    hipLaunchKernelGGL((maxsim_argmax_kernel<KS, NB, WPW, DIRECT, false>), grid, block, 0, stream,
+                       args, args.off);
   return hipGetLastError();
 }
 

@@ -137,6 +137,33 @@ __device__ __forceinline__ float half32_sum(float v) {
   return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);  // the two rows of the half-wave
 }
 
+// Document end of packed queries: the slot maxima m (block b's in lane col of both halves; `slots`
+// is the wave's own LDS row of 32 NB floats) summed per query, each half-wave taking every other
+// one.  A query's slots are read back in the lanes that whole blocks would hold them in, so its sum
+// has the same bits as when it has blocks of its own.  put(ql, sum) is called in one lane of each.
+template <int NB, class Put>
+__device__ __forceinline__ void packed_sums(const MaxsimArgs& a, const float (&m)[NB], float* slots,
+                                            int lane, Put put) {
+  const int col = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    if (half == (b & 1)) slots[b * 32 + col] = m[b];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (a wave's LDS accesses are in order)
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
+  for (int q = 0; q < a.qpw; q += 2) {
+    const int ql = q + half;
+    float qs = 0.f;
+    for (int i0 = 0; i0 < a.lq; i0 += 32) {
+      const int i = i0 + col;
+      qs += half32_sum(ql < a.qpw && i < a.lq ? slots[ql * a.lqp + i] : 0.f);
+    }
+    if (col == 0 && ql < a.qpw) put(ql, qs);
+  }
+  __builtin_amdgcn_wave_barrier();  // the row is rewritten by the next document
+}
+
 // Workgroups of maxsim_argmax_kernel per CU: two by registers (its launch bounds), fewer when
 // two stages and the result ring do not fit the CU's 160 KiB of LDS twice.
 constexpr int argmax_tps(int ks) { return ks >= 8 ? 2 : ks == 4 ? 4 : 8; }
@@ -144,7 +171,7 @@ constexpr int argmax_resident(int ks) {
   const int tile = 32 * (ks * 32 + 16);
   const int tps = argmax_tps(ks);
   const int nb = ks == 16 ? 1 : 2;
-  const int res = 3 * tps * (4 * nb + 4 * nb * 32 * 2);
+  const int res = 3 * tps * (4 * nb * 2 * 4 + 4 * nb * 32 * 2) + 4 * nb * 32 * 4;  // packed
   const int by_lds = (160 * 1024) / (2 * tps * tile + res);
   return by_lds < 2 ? by_lds : 2;
 }

@@ -149,6 +149,37 @@ def test_maxsim_small_grids(nq, lq, dim, n_docs, ld_max):
     assert torch.equal(S[:half], hpr.maxsim_score(args[0][:half].contiguous(), *args[1:]))
 
 
+@pytest.mark.parametrize("nq,lq,dim", [
+    (100, 20, 128), (70, 40, 128), (33, 33, 64), (200, 5, 128), (130, 16, 96), (70, 17, 256),
+    (600, 24, 128), (2100, 42, 128),  # the last one: persistent passes
+])
+def test_maxsim_packed_queries(nq, lq, dim):
+    # many queries whose length is no multiple of 32 share blocks of query slots; a call of few
+    # queries gives each blocks of its own, and the scores must have the same bits
+    g = torch.Generator().manual_seed(nq + lq)
+    lens = torch.randint(1, 90, (230,), generator=g).tolist()
+    Q, D, off = _ragged(nq * lq, nq, lq, lens, dim)
+    Qd, Dd, od = _to_dev(Q, D, off)
+    S = hpr.maxsim_score(Qd, Dd, od)
+    pick = [0, 1, nq // 2, nq - 2, nq - 1]
+    O = oracle.maxsim_scores(_bf(Q[pick]), _bf(D), off.numpy())
+    _assert_close(S[pick].cpu().numpy(), O, rel=1e-4, what="scores")
+    for q in range(0, nq, max(1, nq // 16)):
+        assert torch.equal(S[q:q + 1], hpr.maxsim_score(Qd[q:q + 1].contiguous(), Dd, od))
+
+
+@pytest.mark.parametrize("nq,lq,dim", [(30, 20, 128), (50, 7, 64), (40, 21, 32)])
+def test_loss_packed_queries(nq, lq, dim):
+    g = torch.Generator().manual_seed(nq + lq)
+    lens = torch.randint(1, 90, (61,), generator=g).tolist()
+    Q, D, off = _ragged(nq * lq + 1, nq, lq, lens, dim)
+    pos = torch.randint(0, len(lens), (nq,), generator=g, dtype=torch.int32)
+    _loss_parity(Q, D, off, pos, 1.5625)
+    Qd, Dd, od, pd = _to_dev(Q, D, off, pos)
+    r = hpr.coltrast_loss_fwd_bwd(Qd, Dd, od, pd, 2.0, return_scores=True)
+    assert torch.equal(r["scores"], hpr.maxsim_score(Qd, Dd, od))
+
+
 @pytest.mark.parametrize("nq,n_docs,ld_max", [(3, 5, 40), (24, 48, 300), (100, 800, 40)])
 def test_loss_small_grids(nq, n_docs, ld_max):
     # argmax ranges below 1,024 tokens, and a grid cut to one whole round (13 query groups)
