@@ -41,9 +41,12 @@ namespace {
 // per-read address arithmetic) and the 16 rows of a read phase start 16 bytes apart modulo the
 // 256-byte bank width (conflict-free); a stage holds kTps tiles.
 //
-// DIRECT (dim 128 with 128 query slots per wave, the many-query grids): the tiles go straight
-// from global memory into LDS (buffer loads with the LDS as destination), one tile per wave and
-// stage, so a stage holds WPW tiles.  A wave load writes 1 KiB of consecutive LDS bytes, so a
+// DIRECT (dim 64, 96, 128 or 256, whose rows fill every chunk, with all the query slots a wave can
+// hold: the many-query grids): the tiles go straight from global memory into LDS (buffer loads with
+// the LDS as destination), one tile per wave and stage, so a stage holds WPW tiles (dim 256: two,
+// each loaded by two waves).  1,024 x 32 queries against 20,000 documents: dim 64 13.17 -> 13.04 ms
+// against staging through VGPRs, dim 256 53.2 -> 52.7, and dim 96, whose six k-steps have no VGPR
+// staging (12 chunks a row) and took eight, 22.3 -> 18.4.  A wave load writes 1 KiB of consecutive LDS bytes, so a
 // tile's region is rounded up to whole loads; the lanes that land on a row's padding or past
 // the tile's 32 rows load row 0 of the tile into bytes nobody reads.
 template <int KS, bool DIRECT = false, int WPW = 4>
@@ -53,7 +56,8 @@ struct TileGeom {
   static constexpr int kTileB = 32 * kRowB;        // bytes per tile
   static constexpr int kLoads = (kTileB + 1023) / 1024;             // direct loads per tile
   static constexpr int kTileS = DIRECT ? kLoads * 1024 : kTileB;    // tile stride in a stage
-  static constexpr int kTps = DIRECT ? WPW : KS >= 8 ? 2 : 4;       // tiles per stage
+  static constexpr int kTps = KS == 16 ? 2 : DIRECT ? WPW : KS >= 8 ? 2 : 4;  // tiles per stage
+  static constexpr int kWpt = DIRECT ? WPW / kTps : 1;              // waves that load a tile
 };
 
 
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
   constexpr int kSlotsWG = WPW * NB * 32;
   constexpr int kTps = G::kTps;
   constexpr int kQueries = kSlotsWG / (PACKED ? 16 : 32);  // at most, per workgroup
-  static_assert(!DIRECT || NB == 4, "direct staging: the many-query variant (ordinary loads)");
+  static_assert(!DIRECT || NB == (KS == 16 ? 2 : 4), "direct staging: many queries (ordinary loads)");
   // as many resident workgroups as the plan assumes (maxsim_resident): two stages and the ring
   static_assert((maxsim_waves(KS, NB) * 4 / WPW) *
                         (2 * kTps * G::kTileS + 3 * kTps * kQueries * 4 + (PACKED ? kSlotsWG * 4 : 4) + 4) <=
@@ -224,18 +228,19 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
     const uint32_t r = (uint32_t)row < rmx ? (uint32_t)row : rmx;
     return (row < 32 && c < G::kCpr) ? r * (uint32_t)(32 * KS) + 16u * (uint32_t)c : 0u;
   };
-  // direct staging: wave w loads tile w of the stage, whose first token is r0 and last row rmx
-  // (the lane offsets are recomputed per stage: kept, they would cost registers this kernel
+  // direct staging: wave w loads its share of tile w / kWpt of the stage, whose first token is r0 and
+  // last row rmx (the lane offsets are recomputed per stage: kept, they would cost registers this kernel
   // does not have)
   auto issue_tile = [&](int buf, int r0, uint32_t rmx) {
     const char* tptr = reinterpret_cast<const char*>(a.d) + (uint64_t)(uint32_t)r0 * row_bytes;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(tptr), (short)0, 0x7fffffff, 0x00020000);
-    unsigned char* dst = &lds[buf][wave * G::kTileS];
+    unsigned char* dst = &lds[buf][(wave / G::kWpt) * G::kTileS];
 #pragma unroll
     for (int q = 0; q < G::kLoads; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
-                                               (int)direct_off(q, rmx), 0, 0, 0);
+      if (q % G::kWpt == wave % G::kWpt)  // uniform
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
+                                                 (int)direct_off(q, rmx), 0, 0, 0);
   };
   auto fetch_stage = [&](StageDesc& sd, int buf) {
     sd.d0 = prod.d;
@@ -251,7 +256,7 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
       const uint32_t rmx = ok ? prod.len - prod.t * 32 - 1 : 0;  // later rows repeat the last
       const char* tptr = reinterpret_cast<const char*>(a.d) + (uint64_t)(uint32_t)r0 * row_bytes;
       if constexpr (DIRECT) {
-        if (j == wave) {  // uniform
+        if (j == wave / G::kWpt) {  // uniform
           my_ok = ok;
           my_r0 = r0;
           my_rmx = rmx;
@@ -544,7 +549,12 @@ hipError_t launch_variant(const MaxsimPlan& plan, const MaxsimArgs& args, bool a
     case 2 * 8 + 4: return launch_t<2, 4, 4>(plan, args, stream);
     case 4 * 8 + 1: return launch_t<4, 1, 4>(plan, args, stream);
     case 4 * 8 + 2: return launch_t<4, 2, 4>(plan, args, stream);
-    case 4 * 8 + 4: return launch_t<4, 4, 4>(plan, args, stream);
+    case 4 * 8 + 4:
+      return args.dim == 64 ? launch_t<4, 4, 4, true>(plan, args, stream)
+                            : launch_t<4, 4, 4>(plan, args, stream);
+    case 6 * 8 + 4:
+      return plan.wpw == 8 ? launch_t<6, 4, 8, true>(plan, args, stream)
+                           : launch_t<6, 4, 4, true>(plan, args, stream);
     case 8 * 8 + 1: return launch_t<8, 1, 4>(plan, args, stream);
     case 8 * 8 + 2: return launch_t<8, 2, 4>(plan, args, stream);
     case 8 * 8 + 4:
@@ -554,7 +564,9 @@ hipError_t launch_variant(const MaxsimPlan& plan, const MaxsimArgs& args, bool a
       return plan.wpw == 8 ? launch_t<8, 4, 8>(plan, args, stream)
                            : launch_t<8, 4, 4>(plan, args, stream);
     case 16 * 8 + 1: return launch_t<16, 1, 4>(plan, args, stream);
-    case 16 * 8 + 2: return launch_t<16, 2, 4>(plan, args, stream);
+    case 16 * 8 + 2:
+      return args.dim == 256 ? launch_t<16, 2, 4, true>(plan, args, stream)
+                             : launch_t<16, 2, 4>(plan, args, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -576,6 +588,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
   if (dim < 8 || dim > 256 || dim % 8 != 0 || lq < 1 || nq < 1 || n_docs < 1) return false;
   p->ks = dim <= 32 ? 2 : dim <= 64 ? 4 : dim <= 128 ? 8 : 16;
   p->nb = argmax ? (p->ks == 16 ? 1 : 2) : (p->ks == 16 ? 2 : 4);
+  if (argmax && dim == 96) p->ks = 6;
   p->lqp = (lq + 31) / 32 * 32;
   p->wpw = 4;
   const int lqb = p->lqp / 32;
@@ -615,6 +628,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     p->nb /= 2;
     round = group();
   }
+  if (!argmax && dim == 96 && p->nb == 4) p->ks = 6;  // (no VGPR staging at 6 k-steps)
   const int occ = (int)(round / cus);
   // Workgroups: the plain score takes enough to fill every CU's resident slots 32 times over
   // (short ranges keep the workgroups sharing a range in step, so the range is served from L2);
@@ -669,7 +683,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
       p->own_ranges = p->by_count = false;
       p->n_ranges = 8;
       p->grid = (int64_t)8 * slots;
-      if (p->ks == 8 && p->nb == 4 && occ % 2 == 0) {
+      if ((p->ks == 8 || p->ks == 6) && p->nb == 4 && occ % 2 == 0) {
         const int64_t groups8 = (nq + (int64_t)p->qpw * 8 - 1) / ((int64_t)p->qpw * 8);
         const int slots8 = slots / 2;
         if (fits(groups8, slots8)) {

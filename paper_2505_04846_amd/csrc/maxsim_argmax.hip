@@ -15,12 +15,15 @@
 // epilogues (the last tile of a stage finishes in the next stage), and to HBM two stages later,
 // after a barrier has passed behind every epilogue of the stage: a ring of three result buffers.
 //
-// Staging.  At dim 128 the tiles go straight from global memory into LDS (buffer loads with
-// the LDS as destination), four tiles per stage, wave w loading tile w: the loads of stage s + 1
+// Staging.  At dim 64, 96, 128 and 256 (rows that fill every chunk) the tiles go straight from
+// global memory into LDS (buffer loads with the LDS as destination), four tiles per stage, wave w
+// loading tile w (two per stage and two waves a tile at dim 256): the loads of stage s + 1
 // are issued when stage s starts, into the buffer stage s - 1 used, and each wave waits for its
 // own before the stage's closing barrier.  Against staging through VGPRs (two tiles per stage,
 // the registers the wider stage would need are not there) this halves the barriers and the
 // per-stage bookkeeping per tile and drops the LDS stores.  The other dims keep the VGPR path.
+// A training step of 64 x 32 queries and 512 x 256 tokens: dim 64 98.4 -> 95.9 us, dim 256 253 ->
+// 237, dim 96 (six k-steps instead of eight) 127.6 -> 115.5.
 //
 // Everything else (query operands in VGPRs, the document tile stream, the C layout, the K
 // permutation, XCD placement) is as in maxsim_kernel (maxsim.hip).
@@ -45,7 +48,7 @@ struct ArgGeom {
   static constexpr int kTileB = 32 * kRowB;
   static constexpr int kLoads = (kTileB + 1023) / 1024;  // direct loads per tile
   static constexpr int kTileS = DIRECT ? kLoads * 1024 : kTileB;  // tile stride in a stage
-  static constexpr int kTps = DIRECT ? 4 : argmax_tps(KS);        // tiles per stage (even)
+  static constexpr int kTps = DIRECT && KS < 16 ? 4 : argmax_tps(KS);  // tiles per stage (even)
   static constexpr int kStageB = kTps * kTileS;
 };
 
@@ -72,7 +75,7 @@ template <int KS, int NB, int WPW, bool DIRECT, bool PACKED>
 __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
     MaxsimArgs a, const int64_t* __restrict__ off) {
   using G = ArgGeom<KS, DIRECT>;
-  static_assert(!DIRECT || G::kTps == WPW, "direct staging: one tile per wave");
+  static_assert(!DIRECT || WPW % G::kTps == 0, "direct staging: a tile per wave or group of waves");
   // two workgroups per CU (what the plan assumes for every variant): two stages and the ring
   static_assert(2 * (2 * G::kStageB + 3 * G::kTps * (WPW * NB * 2 * 4 + WPW * NB * 32 * 2) +
                      WPW * NB * 32 * 4) <=
@@ -184,22 +187,26 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
 #pragma unroll
     for (int q = 0; q < G::kLoads; ++q) doff[q] = direct_off(q, 31u);
   }
-  // direct staging: wave w loads tile w of the stage, whose first token is r0 and last row rmx
+  // direct staging: wave w loads its share of tile w / kWpt of the stage, whose first token is r0 and
+  // last row rmx
+  constexpr int kWpt = DIRECT ? WPW / G::kTps : 1;
   auto issue_tile = [&](int buf, int r0, uint32_t rmx) {
     const char* tptr = reinterpret_cast<const char*>(a.d) + (uint64_t)(uint32_t)r0 * row_bytes;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(tptr), (short)0, 0x7fffffff, 0x00020000);
-    unsigned char* dst = &lds[buf][wave * G::kTileS];
+    unsigned char* dst = &lds[buf][(wave / kWpt) * G::kTileS];
     if (rmx >= 31u) {
 #pragma unroll
       for (int q = 0; q < G::kLoads; ++q)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
-                                                 (int)doff[q], 0, 0, 0);
+        if (q % kWpt == wave % kWpt)  // uniform
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
+                                                   (int)doff[q], 0, 0, 0);
     } else {  // a document's last, partial tile: rows past its end repeat its last token
 #pragma unroll
       for (int q = 0; q < G::kLoads; ++q)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
-                                                 (int)direct_off(q, rmx), 0, 0, 0);
+        if (q % kWpt == wave % kWpt)  // uniform
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * q), 16,
+                                                   (int)direct_off(q, rmx), 0, 0, 0);
     }
   };
   auto fetch_stage = [&](StageDesc& sd, int buf) {
@@ -215,7 +222,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void maxsim_argmax_kernel(
       const int r0 = ok ? prod.base + prod.t * 32 : 0;
       const uint32_t rmx = ok ? prod.len - prod.t * 32 - 1 : 0;
       if constexpr (DIRECT) {
-        if (j == wave) {  // uniform
+        if (j == wave / kWpt) {  // uniform
           my_ok = ok;
           my_r0 = r0;
           my_rmx = rmx;
@@ -530,11 +537,16 @@ hipError_t launch_argmax_variant(const MaxsimPlan& plan, const MaxsimArgs& args,
                                  hipStream_t stream) {
   switch (plan.ks) {
     case 2: return launch_argmax_t<2, 2, 4>(plan, args, stream);
-    case 4: return launch_argmax_t<4, 2, 4>(plan, args, stream);
+    case 4:
+      return args.dim == 64 ? launch_argmax_t<4, 2, 4, true>(plan, args, stream)
+                            : launch_argmax_t<4, 2, 4>(plan, args, stream);
+    case 6: return launch_argmax_t<6, 2, 4, true>(plan, args, stream);  // dim 96
     case 8:
       return args.dim == 128 ? launch_argmax_t<8, 2, 4, true>(plan, args, stream)
                              : launch_argmax_t<8, 2, 4>(plan, args, stream);
-    case 16: return launch_argmax_t<16, 1, 4>(plan, args, stream);
+    case 16:
+      return args.dim == 256 ? launch_argmax_t<16, 1, 4, true>(plan, args, stream)
+                             : launch_argmax_t<16, 1, 4>(plan, args, stream);
     default: return hipErrorInvalidValue;
   }
 }

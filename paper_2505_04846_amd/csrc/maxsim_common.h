@@ -166,7 +166,7 @@ __device__ __forceinline__ void packed_sums(const MaxsimArgs& a, const float (&m
 
 // Workgroups of maxsim_argmax_kernel per CU: two by registers (its launch bounds), fewer when
 // two stages and the result ring do not fit the CU's 160 KiB of LDS twice.
-constexpr int argmax_tps(int ks) { return ks >= 8 ? 2 : ks == 4 ? 4 : 8; }
+constexpr int argmax_tps(int ks) { return ks >= 8 ? 2 : ks >= 4 ? 4 : 8; }
 constexpr int argmax_resident(int ks) {
   const int tile = 32 * (ks * 32 + 16);
   const int tps = argmax_tps(ks);

@@ -168,6 +168,20 @@ def test_maxsim_packed_queries(nq, lq, dim):
         assert torch.equal(S[q:q + 1], hpr.maxsim_score(Qd[q:q + 1].contiguous(), Dd, od))
 
 
+@pytest.mark.parametrize("dim", [64, 88, 96, 104, 256])
+@pytest.mark.parametrize("nq,lq", [(40, 32), (30, 20)])
+def test_directly_staged_dims(dim, nq, lq):
+    # dims 64, 96 and 256 stage their tiles straight into LDS when the queries are many (their
+    # neighbours do not); documents ending at every row of a tile, scores and loss
+    lens = list(range(1, 71))
+    Q, D, off = _ragged(dim + nq, nq, lq, lens, dim)
+    S = hpr.maxsim_score(*_to_dev(Q, D, off))
+    O = oracle.maxsim_scores(_bf(Q), _bf(D), off.numpy())
+    _assert_close(S.cpu().numpy(), O, rel=1e-4, what="scores")
+    pos = torch.arange(nq, dtype=torch.int32) % len(lens)
+    _loss_parity(Q, D, off, pos, 1.5625)
+
+
 @pytest.mark.parametrize("nq,lq,dim", [(30, 20, 128), (50, 7, 64), (40, 21, 32)])
 def test_loss_packed_queries(nq, lq, dim):
     g = torch.Generator().manual_seed(nq + lq)
