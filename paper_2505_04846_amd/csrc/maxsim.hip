@@ -69,7 +69,7 @@ struct TileGeom {
 // store stream, which more resident workgroups keep in flight.
 constexpr int maxsim_waves(int ks, int nb) {
   if (ks == 16) return 2;
-  return nb >= 4 ? 2 : nb == 2 ? 3 : 4;
+  return nb >= 3 ? 2 : nb == 2 ? 3 : 4;
 }
 // Workgroups per CU: the register bound above, and the LDS of two stages plus the result
 // buffers against the CU's 160 KiB.
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
   constexpr int kSlotsWG = WPW * NB * 32;
   constexpr int kTps = G::kTps;
   constexpr int kQueries = kSlotsWG / (PACKED ? 16 : 32);  // at most, per workgroup
-  static_assert(!DIRECT || NB == (KS == 16 ? 2 : 4), "direct staging: many queries (ordinary loads)");
+  static_assert(!DIRECT || NB >= (KS == 16 ? 2 : 3), "direct staging: many queries (ordinary loads)");
   // as many resident workgroups as the plan assumes (maxsim_resident): two stages and the ring
   static_assert((maxsim_waves(KS, NB) * 4 / WPW) *
                         (2 * kTps * G::kTileS + 3 * kTps * kQueries * 4 + (PACKED ? kSlotsWG * 4 : 4) + 4) <=
@@ -266,11 +266,11 @@ __global__ __launch_bounds__(64 * WPW, (maxsim_waves(KS, NB) * 4 / WPW)) void ma
         for (int p = 0; p < kPpt; ++p) {
           const uint32_t row = lr + kRp * p;
           const uint32_t r = row < rmx ? row : rmx;
-          // Few-query variants (NB < 4) have one query group, so no other workgroup reads
+          // Few-query variants (NB < 3) have one query group, so no other workgroup reads
           // the range: streaming loads keep it out of L2.  With several groups the range is
           // re-served from L2 and ordinary loads are faster.
           const char* src = tptr + (r * row_bytes + lboff);
-          stage_regs[(j / kTpp) * kPpt + p] = NB < 4 ? load16_stream(src) : load16(src);
+          stage_regs[(j / kTpp) * kPpt + p] = NB < 3 ? load16_stream(src) : load16(src);
         }
       }
       if (ok) {
@@ -546,17 +546,25 @@ hipError_t launch_variant(const MaxsimPlan& plan, const MaxsimArgs& args, bool a
   switch (plan.ks * 8 + plan.nb) {
     case 2 * 8 + 1: return launch_t<2, 1, 4>(plan, args, stream);
     case 2 * 8 + 2: return launch_t<2, 2, 4>(plan, args, stream);
+    case 2 * 8 + 3: return launch_t<2, 3, 4>(plan, args, stream);
     case 2 * 8 + 4: return launch_t<2, 4, 4>(plan, args, stream);
     case 4 * 8 + 1: return launch_t<4, 1, 4>(plan, args, stream);
     case 4 * 8 + 2: return launch_t<4, 2, 4>(plan, args, stream);
+    case 4 * 8 + 3:
+      return args.dim == 64 ? launch_t<4, 3, 4, true>(plan, args, stream)
+                            : launch_t<4, 3, 4>(plan, args, stream);
     case 4 * 8 + 4:
       return args.dim == 64 ? launch_t<4, 4, 4, true>(plan, args, stream)
                             : launch_t<4, 4, 4>(plan, args, stream);
+    case 6 * 8 + 3: return launch_t<6, 3, 4, true>(plan, args, stream);
     case 6 * 8 + 4:
       return plan.wpw == 8 ? launch_t<6, 4, 8, true>(plan, args, stream)
                            : launch_t<6, 4, 4, true>(plan, args, stream);
     case 8 * 8 + 1: return launch_t<8, 1, 4>(plan, args, stream);
     case 8 * 8 + 2: return launch_t<8, 2, 4>(plan, args, stream);
+    case 8 * 8 + 3:
+      return args.dim == 128 ? launch_t<8, 3, 4, true>(plan, args, stream)
+                             : launch_t<8, 3, 4>(plan, args, stream);
     case 8 * 8 + 4:
       if (args.dim == 128)
         return plan.wpw == 8 ? launch_t<8, 4, 8, true>(plan, args, stream)
@@ -618,6 +626,17 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     return (int64_t)cus * (argmax ? msim::argmax_resident(p->ks)
                                   : msim::maxsim_resident(p->ks, p->nb));
   };
+  // Three blocks per wave where they multiply clearly fewer slots than four: 9 to 12 queries of 32
+  // tokens fill the four waves of a workgroup evenly instead of leaving one or two idle (9 queries x
+  // 20,000 documents 414 -> 354 us, 20 queries 720 -> 667, 100 of 96 tokens 9.12 -> 7.53 ms; a
+  // sixteenth fewer, 82 queries: 2.30 -> 2.22).
+  if (p->nb == 4 && lqb <= 3) {
+    group();
+    const int64_t cost4 = 4 * (int64_t)p->n_qgroups;
+    p->nb = 3;
+    group();
+    if (3 * (int64_t)p->n_qgroups * 16 > cost4 * 15) p->nb = 4;
+  }
   // Ranges of the smallest allowed length, and whether the call fills one round of resident
   // workgroups with them.  A score call that does not takes fewer query blocks per wave (more
   // query groups, each with less to do per tile).
@@ -628,7 +647,7 @@ bool maxsim_plan(int nq, int lq, int64_t n_docs, int64_t n_tok, int dim, bool ar
     p->nb /= 2;
     round = group();
   }
-  if (!argmax && dim == 96 && p->nb == 4) p->ks = 6;  // (no VGPR staging at 6 k-steps)
+  if (!argmax && dim == 96 && p->nb >= 3) p->ks = 6;  // (no VGPR staging at 6 k-steps)
   const int occ = (int)(round / cus);
   // Workgroups: the plain score takes enough to fill every CU's resident slots 32 times over
   // (short ranges keep the workgroups sharing a range in step, so the range is served from L2);

@@ -133,6 +133,8 @@ def test_maxsim_scores_few_queries(nq, lq, dim, n_docs):
     (1, 32, 128, 3000, 380),    # about one resident round: own ranges
     (40, 32, 128, 1100, 380),   # between one and two rounds: cut to whole ones
     (2, 32, 128, 9000, 380),    # several rounds: the partition table
+    (12, 32, 128, 4000, 200), (20, 30, 96, 4000, 200), (9, 96, 128, 2500, 200),  # three blocks per
+    (11, 32, 64, 4000, 200), (10, 25, 32, 4000, 200), (12, 32, 80, 3000, 200),   # wave, every staging
 ])
 def test_maxsim_small_grids(nq, lq, dim, n_docs, ld_max):
     # the plans of calls that do not fill the chip with ranges of 1,024 tokens; the no-workspace
