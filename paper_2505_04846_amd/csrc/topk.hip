@@ -338,18 +338,22 @@ __device__ __forceinline__ void stream_candidates(const float* x, int64_t n, con
     s.hi = t;
   }
   __syncthreads();
-  const float tf = key_score(t);  // v >= tf is score_key(v) >= t (a NaN entry is no candidate)
+  // Among numbers v >= tf is score_key(v) >= t.  A NaN's key lies above or below every number's, by
+  // its sign: a row that holds one takes the slow path, which compares keys only.
+  const float tf = key_score(t);
   float mx = tf;
+  bool nan = false;
   if (ends) {
     const int64_t tail = r.head + 4 * r.nv;
     const int64_t i = tid < r.head ? tid : tail + tid - r.head;
-    if (i < n && x[i] >= tf) {
+    if (i < n && !(x[i] < tf)) {
       const uint32_t p = atomicAdd(&s.n_cand, 1u);
       if (p < (uint32_t)kCap) {
         cval[p] = x[i];
         cidx[p] = (uint32_t)i;
       }
       mx = x[i];
+      nan = x[i] != x[i];
     }
   }
   // Per wave and half batch: the ballots of its 16 x 64 tests, held in scalar registers, whose count
@@ -376,7 +380,7 @@ __device__ __forceinline__ void stream_candidates(const float* x, int64_t n, con
         const uint64_t in = __ballot(base + (int64_t)(h * kHalf + u) * kThreads + tid < j1);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          pass[4 * u + c] = __ballot(v[h * kHalf + u][c] >= tf) & in;
+          pass[4 * u + c] = __ballot(!(v[h * kHalf + u][c] < tf)) & in;
           count += (uint32_t)__popcll(pass[4 * u + c]);
         }
       }
@@ -397,12 +401,14 @@ __device__ __forceinline__ void stream_candidates(const float* x, int64_t n, con
             cval[at] = v[h * kHalf + u][c];
             cidx[at] = i0 + (uint32_t)(4 * kThreads * (h * kHalf + u) + c);
             mx = fmaxf(mx, v[h * kHalf + u][c]);
+            nan = nan || v[h * kHalf + u][c] != v[h * kHalf + u][c];
           }
           p += (uint32_t)__popcll(m);
         }
       }
     }
   }
+  if (__any(nan) && lane == 0) atomicMax(&s.n_cand, (uint32_t)kCap + 1u);
   merge_range(t, score_key(mx), s);
 }
 

@@ -315,3 +315,28 @@ def test_dense_topk_workspace_and_errors():
     s1, i1 = hpr.dense_ip_topk(Q, X, 5, ws=ws)
     s2, i2 = hpr.dense_ip_topk(Q, X, 5, ws=ws)
     assert torch.equal(s1, s2) and torch.equal(i1, i2)
+
+
+@pytest.mark.parametrize("n", [8_000, 20_000, 70_000])
+def test_dense_store_all_infinite_and_nan_rows(n):
+    """Rows of infinite and NaN scores, in lists held whole, streamed, and streamed in slices: an
+    infinity orders as a number, a NaN by its sign above or below all of them, at every size."""
+    nq, dim, k = 3, 64, 40
+    Q, X = _rows(nq, dim, 71), _rows(n, dim, 72)
+    Q[:, 0] = 0.5
+    nans, inf, ninf = [17, n - 2], n // 2, n // 3
+    special = nans + [inf, ninf]
+    X[special] = 0.0
+    O = oracle.dense_scores(_f16(Q), _f16(X))
+    O[:, special] = -1e6
+    X[inf, 0], X[ninf, 0] = float("inf"), float("-inf")
+    X[nans, 0] = float("nan")
+    s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    some, _ = hpr.dense_ip_topk(Q.to(DEV), X[:64].to(DEV), 64)  # the sign this unit gives a NaN
+    above = bool(torch.isnan(some[0, 0]).item())
+    lead = (nans if above else []) + [inf]
+    for q in range(nq):
+        assert i[q, :len(lead)].tolist() == lead
+        assert np.isnan(s[q]).sum() == len(lead) - 1 and s[q, len(lead) - 1] == np.inf
+        check_topk(s[q, len(lead):], i[q, len(lead):], O[q], k - len(lead), rel=REL)
