@@ -256,8 +256,11 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
         def step():
             ws_out["scores"], ws_out["idx"] = hpr.dense_ip_topk(Q, X, k, ws=ws)
 
-        sample_rows = min(n, max(131072, 32 * k))
-        flops = 2.0 * dim * nq * float(n - sample_rows)  # the filtered scan over rows [S, n)
+        # the filtered scan covers the rows past the sample; a call of at most 2^26 scores scores
+        # and stores every row in one launch instead
+        stored = nq * n <= 1 << 26
+        scanned = float(n if stored else n - min(n, max(131072, 32 * k)))
+        flops = 2.0 * dim * nq * scanned
 
         def cpu_sample():
             # The oracle on the first queries against consecutive row chunks of the store until
@@ -297,9 +300,10 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
             r = hpr.retrieval_metrics(ws_out["idx"][pq].contiguous(), pr.contiguous(), k)
             m = r["metrics"].cpu().tolist()
             return {"queries": int(pq.numel()), "k": k, "p_at_k": m[0], "mrr_at_k": m[1]}
-        # the scan's algorithmic bytes: rows [S, n) and the queries read once
-        sbytes = 2.0 * dim * float(n - sample_rows) + 2.0 * nq * dim
-        return dict(step=step, pairs=nq, kernel="dense_scan", flops=flops, bytes=sbytes, after=after,
+        # that launch's algorithmic bytes: its rows and the queries read once, stored scores written
+        sbytes = 2.0 * dim * (scanned + nq) + (4.0 * nq * n if stored else 0.0)
+        return dict(step=step, pairs=nq, kernel="dense_sample" if stored else "dense_scan",
+                    flops=flops, bytes=sbytes, after=after,
                     metric="top-k queries/sec + % fp16 MFMA peak",
                     cpu_sample=cpu_sample, config=cfg, dtype="fp16", unit="queries/s",
                     sha=source_sha("dense.hip", "common.h", "kernels.h"))
