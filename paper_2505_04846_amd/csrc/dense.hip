@@ -2,8 +2,8 @@
 //
 // s[q, r] = <Q[q], X[r]> (fp16 MFMA, fp32 accumulate); the k best rows per query under
 // (score desc, row asc).  Calls of few scores (dense_plan: the store no longer than the sample
-// below, or at most kDenseStoreAll scores) store them all and select from them.  Otherwise the
-// score matrix is never materialised:
+// below, or at most kDenseStoreAll scores of at most kDenseStoreRows rows) store them all and select
+// from them.  Otherwise the score matrix is never materialised:
 //
 //   1. Sample.  Rows [0, S) are scored exactly into a workspace matrix and the row top-k of it
 //      is taken (the radix select of topk.hip).  Its k-th score theta_q is a lower bound on the

@@ -124,7 +124,13 @@ hipError_t launch_scale_grads(const float* dq, int64_t n_q, uint16_t* dq_out, co
 // Up to kDenseStoreAll scores (256 MiB) are all stored and selected from: the sample's filter and
 // the idle launches of the exact fallback cost about 110 us a call, the scores' two trips less
 // (150 queries x 400,000 rows x 384: 221 us against 236; 200 queries: 234 either way).
+// Not past kDenseStoreRows rows: the select takes its bound from the 16th of 16,384 sampled keys or
+// a later one, so about n / 1024 entries reach it, a quarter of its list's 8,192 places at 2^21 rows
+// (with k above 512 a half), all of them at 8.4 million; a row whose list overflows is walked whole by
+// one workgroup.  One query, dim 64, k = 100: 2,097,152 rows 105 us stored, 200 filtered; 8 million
+// 18.0 ms against 0.58; 60 million 134 against 3.9.
 constexpr int64_t kDenseStoreAll = (int64_t)1 << 26;
+constexpr int64_t kDenseStoreRows = (int64_t)1 << 21;
 struct DensePlan {
   int64_t S;
   int64_t cap;
@@ -132,7 +138,8 @@ struct DensePlan {
 inline DensePlan dense_plan(int nq, int64_t n, int k) {
   DensePlan p;
   const int64_t target = (int64_t)32 * k > 131072 ? (int64_t)32 * k : 131072;
-  p.S = n < target || (int64_t)nq * n <= kDenseStoreAll ? n : target;
+  const bool store_all = n <= kDenseStoreRows && (int64_t)nq * n <= kDenseStoreAll;
+  p.S = n < target || store_all ? n : target;
   if (p.S == n) {
     p.cap = 0;
   } else {

@@ -208,6 +208,16 @@ def test_workspace_sizes_are_consistent():
     assert lib.maxsim_score_workspace_size(64, 32, 0, 0, 128) == 0
 
 
+@pytest.mark.parametrize("nq,n", [(1, 10_000_000), (4, 16_400_000), (1, 60_000_000)])
+def test_dense_long_stores_keep_no_score_matrix(nq, n):
+    # past 2^21 rows the select's list may not hold what its bound lets through: few queries over
+    # long stores take the filter, however few scores there are
+    lib = hpr.lib()
+    assert nq * n <= 1 << 26
+    assert lib.dense_ip_topk_workspace_size(nq, n, 64, 100) < 4 * nq * n
+    assert lib.dense_ip_topk_workspace_size(1, 1 << 21, 64, 100) >= 4 << 21
+
+
 def test_csr_validate_and_scale_reject_null():
     lib = hpr.lib()
     bad = ctypes.c_int64(0)

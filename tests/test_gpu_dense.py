@@ -290,6 +290,33 @@ def test_dense_topk_select(nq, n, k, kind):
         assert np.array_equal(s[q] * 1024, sign * v[order])
 
 
+@pytest.mark.parametrize("nq,n,filtered", [(2, 1 << 21, False), (2, (1 << 21) + 1, True),
+                                           (3, 10_000_019, True)])
+def test_dense_topk_long_store(nq, n, filtered):
+    # few queries over a long store: exact order on both sides of the longest stored rows, and the
+    # filter beyond (the select alone would have one workgroup walk a row of ten million)
+    k = 100
+    v = _exact_scores("normal", n, np.random.default_rng(n))
+    X = np.zeros((n, 8), dtype=np.float16)
+    X[:, 0], X[:, 1] = v >> 10, v & 1023
+    Q = np.zeros((nq, 8), dtype=np.float16)
+    Q[:, 0], Q[:, 1] = 1.0, 2.0 ** -10
+    Q[1::2] *= -1
+    Qd, Xd = torch.from_numpy(Q).to(DEV), torch.from_numpy(X).to(DEV)
+    hpr.kernel_timing(True)
+    hpr.kernel_timing_read("dense_scan")
+    s, i = hpr.dense_ip_topk(Qd, Xd, k)
+    scans = hpr.kernel_timing_read("dense_scan")[1]
+    hpr.kernel_timing(False)
+    assert scans == (1 if filtered else 0)
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    for q in range(nq):
+        sign = -1 if q % 2 else 1
+        order = np.argsort(-sign * v, kind="stable")[:k]
+        assert np.array_equal(i[q], order), f"query {q}"
+        assert np.array_equal(s[q] * 1024, sign * v[order])
+
+
 def test_dense_topk_planted_rows_rank_first():
     w = synth.dense_retrieval(seed=0, device=DEV, nq=512, n=300_000, dim=512, k=10, n_planted=200)
     s, i = hpr.dense_ip_topk(w["Q"], w["X"], w["k"])
