@@ -4,7 +4,7 @@
 // to break ties by lower index, the 64-bit key (score key << 32) | ~index (unique per row).
 //
 // Fast path (one pass over the row):
-//   1. Sample.  About one score in 64 (up to 16384), in evenly spaced runs of 64 entries; a bound
+//   1. Sample.  About one score in 64 (up to 16384), in evenly spaced runs of 8 entries; a bound
 //      t that about `want` sample keys reach (want chosen so that the expected number of row
 //      entries at or above t lies well inside [k, kCap], see below).
 //   2. Stream.  Every entry with key >= t is appended to an LDS candidate list (kCap entries).
@@ -35,7 +35,8 @@ constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxK = 1024;
 constexpr int kCap = 8192;      // LDS candidate list (keys and indices: 64 KiB)
-constexpr int kMaxRuns = 2 * kCap / 64;  // sample: up to 256 runs of 64 entries (16384 keys)
+constexpr int kRun = 8;         // sample: runs of 8 entries (two vectors), one run in 512 entries
+constexpr int kMaxRuns = 2 * kCap / kRun;  // at most 2048 of them (16384 keys)
 constexpr int kUnroll = 8;      // 16-byte loads in flight per thread while streaming
 constexpr int kBinBits = 11;
 constexpr int kBins = 1 << kBinBits;  // two per thread
@@ -281,26 +282,33 @@ __device__ __forceinline__ RowVec row_vec(const float* x, int64_t n) {
   return r;
 }
 
-// Step 1: nr runs of 16 aligned 16-byte vectors (64 entries), run r starting at vector r * nv / nr
-// of the row's aligned part (nv >= 16 nr, so runs do not overlap); about one entry in 64 is
-// sampled, at most kMaxRuns runs.  The bound is one that about want sample keys reach (up to an
-// eighth more): about want * n / ns row entries do, with a relative spread of about 1 / sqrt(want).
-// Aimed at 8 k entries, between 1024 and 4096: at 4096 want is 64 and the spread 512, so k <= 1024
-// and kCap are six standard deviations away; at 1024 want is 16, and fewer than k <= 128 or more
-// than kCap entries as unlikely.  On rows longer than kMaxRuns * 4096 the sample is thinner and
-// want at least 16 (a wider spread).
+// Step 1: nr runs of kRun entries, run r starting at vector r * nv / nr of the row's aligned part
+// (nv >= 2 nr, so runs do not overlap); about one entry in 64 is sampled, at most kMaxRuns runs.
+// The bound is one that about want sample keys reach (up to an eighth more): about want * n / ns row
+// entries do, with a relative spread of about 1 / sqrt(want).  Aimed at 8 k entries, between 1024 and
+// 4096: at 4096 want is 64 and the spread 512, so k <= 1024 and kCap are six standard deviations away;
+// at 1024 want is 16, and fewer than k <= 128 or more than kCap entries as unlikely.  On rows longer
+// than 2^20 the sample is thinner while want is at least 16: about n / 1024 entries reach the bound,
+// so the list overflows often past 5 million and nearly always past 8.4 million.
+// The runs are shorter than want because neighbours score alike: a paper's chunks lie together, and
+// where one paper outscores the rest, its entries in the sample are those of the runs inside it.  With
+// runs of 64 and want = 16, a run inside a paper of 64 to 400 chunks put the bound so high that fewer
+// than k = 100 of them reached it, and the row took the slow path: 64 queries, each with such a paper
+// of 200 chunks among 1,000,000 rows, took 1520 us instead of 66.  Runs of 8 can only do so where
+// want / 8 of them fit, in a cluster of more than k entries.
 __device__ __forceinline__ uint32_t sample_bound(const RowVec& r, int64_t n, int k, TopkShared& s) {
   const int tid = threadIdx.x;
-  const int nr = (n + 4095) / 4096 < kMaxRuns ? (int)((n + 4095) / 4096) : kMaxRuns;
-  const int ns = 64 * nr;
+  constexpr int kVec = kRun / 4, kPer = 64 * kRun;
+  const int nr = (n + kPer - 1) / kPer < kMaxRuns ? (int)((n + kPer - 1) / kPer) : kMaxRuns;
+  const int ns = kRun * nr;
   if (tid == 0) {
     s.lo = ~0u;
     s.hi = 0u;
   }
   __syncthreads();
   uint32_t mn = ~0u, mx = 0u;
-  for (int u = tid; u < 16 * nr; u += kThreads) {
-    const f32x4 v = r.v[(int64_t)(u >> 4) * r.nv / nr + (u & 15)];
+  for (int u = tid; u < kVec * nr; u += kThreads) {
+    const f32x4 v = r.v[(int64_t)(u / kVec) * r.nv / nr + u % kVec];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const uint32_t key = score_key(v[c]);

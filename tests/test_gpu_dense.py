@@ -290,6 +290,42 @@ def test_dense_topk_select(nq, n, k, kind):
         assert np.array_equal(s[q] * 1024, sign * v[order])
 
 
+def _topk_us(Qd, Xd, k):
+    hpr.dense_ip_topk(Qd, Xd, k)
+    hpr.kernel_timing(True)
+    hpr.kernel_timing_read("topk")
+    us = []
+    for _ in range(5):
+        hpr.dense_ip_topk(Qd, Xd, k)
+        us.append(1e3 * hpr.kernel_timing_read("topk")[0])
+    hpr.kernel_timing(False)
+    return min(us)
+
+
+@pytest.mark.parametrize("nq,n,k,cluster", [
+    (64, 1_000_000, 100, 200), (64, 300_000, 100, 100), (512, 131_072, 100, 200),
+    (64, 1_000_000, 1000, 400),
+])
+def test_dense_topk_of_clustered_rows(nq, n, k, cluster):
+    # a paper's chunks lie together: rows whose best scores are neighbours give the same lists as
+    # the shuffled store, and do not send the select through its slow path (15 to 25 times as long)
+    g = torch.Generator(device=DEV).manual_seed(n + nq)
+    Q = synth.unit_rows(nq, 64, g, DEV, torch.float16)
+    X = synth.unit_rows(n, 64, g, DEV, torch.float16)
+    first = torch.randperm(n // cluster - 1, generator=g, device=DEV)[:nq] * cluster + 37
+    for q, a in enumerate(first.tolist()):
+        x = Q[q].float() + 0.06 * torch.randn((cluster, 64), generator=g, device=DEV)
+        X[a:a + cluster] = synth._normalise(x).to(torch.float16)
+    P = X[torch.randperm(n, generator=g, device=DEV)].contiguous()
+    s, i = hpr.dense_ip_topk(Q, X, k)
+    sp, _ = hpr.dense_ip_topk(Q, P, k)
+    assert torch.equal(s, sp)
+    inside = (i >= first[:, None]) & (i < first[:, None] + cluster)
+    assert bool((inside[:, :min(k, cluster)].float().mean(1) > 0.9).all())
+    clustered, shuffled = _topk_us(Q, X, k), _topk_us(Q, P, k)
+    assert clustered <= 3.0 * shuffled, (clustered, shuffled)
+
+
 @pytest.mark.parametrize("nq,n,filtered", [(2, 1 << 21, False), (2, (1 << 21) + 1, True),
                                            (3, 10_000_019, True)])
 def test_dense_topk_long_store(nq, n, filtered):
