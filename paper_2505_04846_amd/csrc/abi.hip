@@ -587,6 +587,7 @@ hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64
   g.r0 = 0;
   g.r1 = p.S;
   g.dim = dim;
+  g.k = k;
   g.scores = sample;
   g.ld = p.S;
   hipError_t e = timed("dense_sample", s, [&] { return launch_dense_gemm(g, n_cu, s); });

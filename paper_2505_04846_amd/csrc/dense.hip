@@ -89,7 +89,7 @@ struct GemmGeom {
 //   skinny  32 x 128, 4 waves of 32 x 32, two workgroups per CU (a ring of four 20 KiB stages)
 //   short   32 x 64, 2 waves of 32 x 32, three workgroups per CU (a ring of four 12 KiB stages)
 //   long    64 x 256, 4 waves of 64 x 64, two workgroups per CU (a ring of four 20 KiB stages of 32
-//           halves): the filtered scan's at 33 to 64 queries, and the fallback's
+//           halves): the filtered scan's up to 64 queries, and the fallback's
 using GeomWide = GemmGeom<256, 256, 4, 2, 64, 2, 1>;
 using GeomMid = GemmGeom<128, 128, 2, 2, 64, 2, 2>;
 using GeomNarrow = GemmGeom<64, 128, 1, 4, 64, 2, 3>;
@@ -788,7 +788,7 @@ hipError_t launch_gemm_grid(GemmArgs a, hipStream_t stream) {
   return e;
 }
 
-enum GemmTile { kWide, kMid, kNarrow, kSkinny, kShort };
+enum GemmTile { kWide, kMid, kNarrow, kSkinny, kShort, kLong };
 
 // The largest tile whose grid still fills the chip.  A larger tile reads the operands fewer times
 // (4096 queries x 131,072 rows x 4096: wide 3.84 ms, mid 4.88, narrow 6.05, skinny 10.0), a tile
@@ -798,20 +798,36 @@ enum GemmTile { kWide, kMid, kNarrow, kSkinny, kShort };
 //   wide from 144 of them: 1000 x 10,000 (160 tiles) wide 29, mid 35, narrow 31; 200 x 25,000 (98)
 //     28, 22, 28; up to 128 queries half of it is padding: 128 x 400,000 x 4096 wide 927, mid 749
 //   mid from 384: 100 x 50,000 (391) mid 22, narrow 28; 100 x 25,000 (196) 19, 16; up to 64
-//     queries 64 x 1,000,000 x 1024 mid 508, narrow 453
+//     queries 64 x 1,000,000 x 1024 mid 508, narrow 453.  Not where a filter of short rows lets many
+//     entries through: a wide tile's waves append more of them per round trip (whole calls, 2,500,000
+//     rows, queries x k, mid against wide): 64 100 x 1000 2370, 2254; 256 100 x 1000 2400, 2283; 8 100 x
+//     100 517, 500; but 256 100 x 100 561, 728; 768 128 x 1000 2516, 2603; 64 128 x 100 514, 514
 //   narrow from 300: 200 x 10,000 (316) narrow 16, skinny 18; 48 x 25,000 (196) 15, 14; up to 32
 //     queries 16 x 1,000,000 x 1024 narrow 397, skinny 395
-//   skinny from 192: 48 x 25,000 (392) skinny 14, short 16; 16 x 10,000 (79) 9.1, 8.5.  Many rounds
-//     of long rows stream best through short tiles: 1 x 1,000,000 x 4096 short 1307, skinny 1334;
-//     at dim 1024 skinny 395, short 400
-int tile_of(int64_t nq, int64_t rows, int dim) {
+//   skinny from 192: 48 x 25,000 (392) skinny 14, short 16; 16 x 10,000 (79) 9.1, 8.5
+// Rows of 4096 halves and more stream best through short tiles once they are 1.6 G halves (whole
+// calls of one query): 4096 x 300,000 skinny 424, short 434; 4096 x 500,000 714, 686; 4096 x 1,000,000
+// 1380, 1335; 8192 x 150,000 443, 460; 8192 x 300,000 862, 853.  Shorter rows never do: 2048 x
+// 1,000,000 669, 692; 1024 x 1,000,000 349, 351.
+// The filter (scans of two million rows and more where the queries are at most 32) takes 64 x 256,
+// long, in place of narrow: a wave's round trips to the candidate lists then serve twice the rows (60 x
+// 3,000,000 x 384: 576 us against narrow's 625).  Up to 32 queries half of it is padding, and skinny
+// is the better one where the rows are long, are no power of two and few entries pass (k n / 131,072
+// of them a query; 4,000,000 rows, whole calls, queries x k, skinny against long): 768 32 x 100 1061,
+// 1176; 768 17 x 300 1439, 1270; 640 32 x 100 910, 1010; 1280 32 x 100 (3,000,000) 1367, 1469; but 512
+// 17 x 100 790, 769; 256 17 x 100 636, 602; 64 1 x 100 324, 301; 64 8 x 1000 1678, 1385; 1024 17 x
+// 100 (12,000,000) 4408, 4074; 2048 17 x 10 (2,500,000) 1876, 1818.
+int tile_of(bool filter, int64_t nq, int64_t rows, int dim, int k) {
   auto grid = [&](int64_t tq, int64_t tr) {
     return ((nq + tq - 1) / tq) * ((rows + tr - 1) / tr);
   };
   if (nq > 128 && grid(256, 256) >= 144) return kWide;
+  if (filter && nq > 64 && nq <= 128 && nq * k > 192 * dim) return kWide;
   if (nq > 64 && grid(128, 128) >= 384) return kMid;
-  if (nq > 32 && grid(64, 128) >= 300) return kNarrow;
-  if (nq <= 32 && dim >= 2048 && rows >= 65536 * 3) return kShort;
+  if (nq > 32 && grid(64, 128) >= 300) return filter ? kLong : kNarrow;
+  if (filter && nq <= 32)
+    return dim >= 640 && (dim & (dim - 1)) != 0 && nq * k <= 5 * dim ? kSkinny : kLong;
+  if (nq <= 32 && dim >= 4096 && rows * dim >= (int64_t)3 << 29) return kShort;
   return grid(32, 128) >= 192 ? kSkinny : kShort;
 }
 
@@ -822,9 +838,10 @@ hipError_t launch_gemm_mode(int tile, const GemmArgs& a, hipStream_t stream) {
     case kMid: return launch_gemm_grid<GeomMid, MODE>(a, stream);
     case kNarrow:
       if constexpr (MODE == kStore) return launch_gemm_grid<GeomNarrow, MODE>(a, stream);
-      // twice the rows per filter epilogue: 60 x 3,000,000 x 384 in 576 us against 625 (60 x
-      // 1,500,000 x 1024: 573 against 583)
-      return launch_gemm_grid<GeomLong, MODE>(a, stream);
+      return hipErrorInvalidValue;
+    case kLong:
+      if constexpr (MODE == kFilter) return launch_gemm_grid<GeomLong, MODE>(a, stream);
+      return hipErrorInvalidValue;
     case kSkinny: return launch_gemm_grid<GeomSkinny, MODE>(a, stream);
     default: return launch_gemm_grid<GeomShort, MODE>(a, stream);
   }
@@ -863,7 +880,7 @@ hipError_t launch_dense_gemm(const DenseGemm& g, int n_cu, hipStream_t stream) {
     if (g.mode == kFilter) return launch_gemm_t<GeomLong, kFilter, true>(a, blocks, stream);
     return hipErrorInvalidValue;
   }
-  const int tile = tile_of(g.nqa, g.r1 - g.r0, g.dim);
+  const int tile = tile_of(g.mode == kFilter, g.nqa, g.r1 - g.r0, g.dim, g.k);
   switch (g.mode) {
     case kStore: return launch_gemm_mode<kStore>(tile, a, stream);
     case kFilter: return launch_gemm_mode<kFilter>(tile, a, stream);

@@ -171,6 +171,7 @@ struct DenseGemm {
   const uint16_t* x;
   int64_t r0, r1;
   int dim;
+  int k;  // filter: the call's k (the tile goes by how many entries pass)
   float* scores;
   int64_t ld;
   const float* theta;

@@ -223,6 +223,70 @@ def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies):
             check_topk(s[q], i[q], O[r], k, rel=REL)
 
 
+def _tile(filtered, nq, rows, dim, k):
+    """The GEMM tile of a launch, as the library chooses it (so that no case drifts off its line)."""
+    def grid(tq, tr):
+        return -(-nq // tq) * -(-rows // tr)
+    if nq > 128 and grid(256, 256) >= 144:
+        return "wide"
+    if filtered and 64 < nq <= 128 and nq * k > 192 * dim:
+        return "wide"
+    if nq > 64 and grid(128, 128) >= 384:
+        return "mid"
+    if nq > 32 and grid(64, 128) >= 300:
+        return "long" if filtered else "narrow"
+    if filtered and nq <= 32:
+        return "skinny" if dim >= 640 and dim & (dim - 1) and nq * k <= 5 * dim else "long"
+    if nq <= 32 and dim >= 4096 and rows * dim >= 3 << 29:
+        return "short"
+    return "skinny" if grid(32, 128) >= 192 else "short"
+
+
+def _filtered(nq, n):
+    return n > SAMPLE_ROWS and (n > 1 << 21 or nq * n > 1 << 26)
+
+
+def _device_rows(n, dim, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    X = torch.empty((n, dim), dtype=torch.float16, device=DEV)
+    for r in range(0, n, 1 << 18):
+        x = torch.randn((min(n - r, 1 << 18), dim), generator=g, device=DEV)
+        X[r:r + (1 << 18)] = synth._normalise(x).to(torch.float16)
+    return X
+
+
+def _scores64(Q, X):
+    """The exact scores of device rows, in 64 bits, on the host."""
+    q = Q.double()
+    return torch.cat([q @ X[r:r + (1 << 18)].double().t().contiguous()
+                      for r in range(0, X.shape[0], 1 << 18)], 1).cpu().numpy()
+
+
+@pytest.mark.parametrize("nq,n,dim,k,tile", [
+    (600, SAMPLE_ROWS + 48 * 256 - 3, 136, 20, "wide"),  # 144 of them; one fewer
+    (600, SAMPLE_ROWS + 47 * 256, 136, 20, "mid"),
+    (100, 700_003, 72, 10, "mid"), (100, 700_003, 72, 138, "mid"), (100, 700_003, 72, 139, "wide"),
+    (65, 1_100_001, 200, 10, "mid"), (64, 1_100_001, 200, 10, "long"), (33, 2_100_001, 136, 20, "long"),
+    (32, 2_100_001, 200, 10, "long"), (1, 2_100_001, 136, 1000, "long"),
+    (32, 2_100_001, 648, 101, "skinny"), (32, 2_100_001, 648, 102, "long"),
+    (3, 2_100_001, 768, 10, "skinny"), (3, 2_100_001, 1024, 10, "long"),
+    (520, SAMPLE_ROWS + 1629, 136, 50, "skinny"), (520, SAMPLE_ROWS + 929, 136, 50, "short"),
+])
+def test_dense_topk_filter_tiles(nq, n, dim, k, tile):
+    # the filter of every tile, on both sides of the lines between them, over several K stages
+    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
+    Q, X = _device_rows(nq, dim, 81 + nq), _device_rows(n, dim, 82 + dim)
+    X[n - 1], X[SAMPLE_ROWS] = Q[nq - 1], Q[0]  # the edges of the scan hold winners
+    s, i = hpr.dense_ip_topk(Q, X, k)
+    s, i = s.cpu().numpy(), i.cpu().numpy()
+    _check_structure(s, i, n, k)
+    assert n - 1 in i[nq - 1] and SAMPLE_ROWS in i[0]
+    pick = sorted({0, nq // 2, nq - 1})
+    O = _scores64(Q[pick], X)
+    for r, q in enumerate(pick):
+        check_topk(s[q], i[q], O[r], k, rel=REL)
+
+
 @pytest.mark.parametrize("nq,n,dim,k", [
     (129, 18_400, 72, 10), (256, 18_177, 64, 10),   # 144 wide tiles, the last one ragged
     (257, 12_000, 40, 10), (128, 49_100, 24, 10),    # one fewer; 384 mid tiles
