@@ -330,9 +330,19 @@ int64_t chunk_groups(int64_t n) {
   return (n + g - 1) / g;
 }
 
+// Past the end of each step of chunk_rows_per_wave there are fewer groups than at it: the largest of
+// the steps' ends below n, so that the workspace of a longer input holds every shorter one's.
 int64_t chunk_groups_most(int64_t n) {
   const int64_t per128 = (n + 127) / 128, g = chunk_groups(n);
-  return g > per128 ? g : per128;
+  int64_t most = g > per128 ? g : per128;
+  auto step = [&](int64_t end) {
+    const int64_t e = n > end ? chunk_groups(end) : 0;
+    most = e > most ? e : most;
+  };
+  for (int64_t r = 1; r < 32; r *= 2) step(r * 12288);
+  step((int64_t)1 << 20);
+  step(((int64_t)1 << 28) - 1);
+  return most;
 }
 
 hipError_t launch_semantic_chunk(const uint16_t* E, int64_t n, int dim, const int64_t* off,

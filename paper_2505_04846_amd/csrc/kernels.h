@@ -210,9 +210,9 @@ hipError_t launch_dense_radix(const int32_t* m_dev, const int32_t* qlist, int nq
 
 // Semantic chunking (chunking.hip): cos_out [n] (NaN at paper starts), seg [n] segment ids,
 // *n_seg the segment count; cnt [chunk_groups(n)] int32 and base [chunk_groups(n)] int64 are
-// scratch (the workspace holds chunk_groups_most(n) of each: never fewer than one per 128
-// sentences, the size callers have been able to count on).  off (paper offsets, n_papers + 1 entries) may be null: one paper.  dim % 8 == 0,
-// 8 <= dim <= kMaxChunkDim.
+// scratch (the workspace holds chunk_groups_most(n) of each: as many as any shorter input needs, and
+// never fewer than one per 128 sentences, the size callers have been able to count on).  off (paper
+// offsets, n_papers + 1 entries) may be null: one paper.  dim % 8 == 0, 8 <= dim <= kMaxChunkDim.
 constexpr int kMaxChunkDim = 4096;
 int chunk_rows_per_wave(int64_t n);  // sentences per wave range
 int64_t chunk_groups(int64_t n);     // workgroups of the scan, four ranges each

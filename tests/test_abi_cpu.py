@@ -171,6 +171,17 @@ def test_semantic_chunk_workspace():
     assert _chunk(n=n, ws_bytes=w - 1) == 5
 
 
+def test_semantic_chunk_workspace_never_shrinks():
+    # a workspace sized for the longest input of a program holds its shorter ones
+    lib = hpr.lib()
+    steps = [12288 << r for r in range(6)] + [1 << 20, 1 << 21, 1 << 28, 1 << 29, (1 << 31) - 1]
+    ns = sorted({max(1, e + d) for e in steps for d in (-129, -1, 0, 1, 129)} | set(range(1, 2000, 7))
+                | {int(1.13 ** i) for i in range(175)})
+    sizes = [lib.semantic_chunk_workspace_size(n, 768) for n in ns if n < 1 << 31]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    assert _chunk(n=12288, dim=768, ws_bytes=lib.semantic_chunk_workspace_size(12288, 768) - 1) == 5
+
+
 def test_retrieval_metrics_rejects():
     lib = hpr.lib()
     f = lib.retrieval_metrics
