@@ -326,7 +326,7 @@ size_t maxsim_topk_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_
   (void)lq, (void)n_tok, (void)dim, (void)k;
   if (nq < 1 || n_docs < 1) return 0;
   return align_up((size_t)nq * (size_t)n_docs * sizeof(float)) + part_bytes(n_docs) +
-         align_up(topk_scratch_bytes(nq, n_docs));
+         align_up(topk_scratch_most(nq, n_docs));
 }
 
 size_t coltrast_loss_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_t n_tok,
@@ -534,12 +534,20 @@ hpr_status hpr_read_calibration(const void* buf, int64_t bytes, uint32_t* sink, 
   return e == hipSuccess ? HPR_OK : hip_fail(e, "read calibration launch");
 }
 
+// The size never falls as nq, n or k grow, though longer and larger calls need less than the largest
+// one that stores its scores: a workspace sized for a program's full batch serves its last one.
 size_t dense_ip_topk_workspace_size(int32_t nq, int64_t n, int32_t dim, int32_t k) {
   if (nq < 1 || n < 1 || dim < 1 || k < 1) return 0;
+  // every score stored, here or in a smaller call
+  const int64_t whole = n < dense_sample_rows(k) ? n : dense_sample_rows(k);
+  int64_t stored = (int64_t)nq * (n < kDenseStoreRows ? n : kDenseStoreRows);
+  if (stored > kDenseStoreAll) stored = kDenseStoreAll;
+  if (stored < nq * whole) stored = nq * whole;
+  const size_t most = align_up((size_t)stored * sizeof(float)) + align_up(topk_scratch_most(nq, n));
   const DensePlan p = dense_plan(nq, n, k);
+  if (p.S == n) return most;
   size_t b = align_up((size_t)nq * (size_t)p.S * sizeof(float)) +  // sample scores
-             align_up(topk_scratch_bytes(nq, p.S));
-  if (p.S == n) return b;
+             align_up(topk_scratch_most(nq, p.S));
   b += align_up((size_t)nq * k * sizeof(float)) + align_up((size_t)nq * k * sizeof(int64_t));
   b += align_up((size_t)nq * sizeof(float)) + align_up((size_t)nq * sizeof(int64_t)) +
        align_up((size_t)nq * sizeof(int32_t));
@@ -549,7 +557,7 @@ size_t dense_ip_topk_workspace_size(int32_t nq, int64_t n, int32_t dim, int32_t 
   b += align_up((size_t)nq * (size_t)dim * sizeof(uint16_t));                   // queued rows
   b += align_up((size_t)nq * 256 * sizeof(uint32_t)) +                          // radix select
        align_up((size_t)nq * sizeof(unsigned long long)) + align_up((size_t)nq * sizeof(uint32_t));
-  return b;
+  return b > most ? b : most;
 }
 
 hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64_t n,

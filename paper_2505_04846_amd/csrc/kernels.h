@@ -58,8 +58,9 @@ hipError_t launch_csr_validate(const int64_t* off, int64_t n_docs, int64_t n_tok
 
 // Exact top-k of each row of a [rows, n] fp32 matrix (row stride ld), sorted (score desc,
 // index asc).  scratch: topk_scratch_bytes(rows, n) bytes, 256-byte aligned (may be null when that
-// is 0).
+// is 0); topk_scratch_most is at least that of any call with no more rows and no longer ones.
 size_t topk_scratch_bytes(int64_t rows, int64_t n);
+size_t topk_scratch_most(int64_t rows, int64_t n);
 hipError_t launch_topk_rows(const float* scores, int64_t rows, int64_t n, int64_t ld, int k,
                             float* out_scores, int64_t* out_idx, void* scratch,
                             hipStream_t stream);
@@ -135,9 +136,12 @@ struct DensePlan {
   int64_t S;
   int64_t cap;
 };
+inline int64_t dense_sample_rows(int k) {
+  return (int64_t)32 * k > 131072 ? (int64_t)32 * k : 131072;
+}
 inline DensePlan dense_plan(int nq, int64_t n, int k) {
   DensePlan p;
-  const int64_t target = (int64_t)32 * k > 131072 ? (int64_t)32 * k : 131072;
+  const int64_t target = dense_sample_rows(k);
   const bool store_all = n <= kDenseStoreRows && (int64_t)nq * n <= kDenseStoreAll;
   p.S = n < target || store_all ? n : target;
   if (p.S == n) {

@@ -614,6 +614,13 @@ size_t topk_scratch_bytes(int64_t rows, int64_t n) {
   return p > 1 ? (size_t)rows * (size_t)p * sizeof(SliceList) : 0;
 }
 
+size_t topk_scratch_most(int64_t rows, int64_t n) {
+  if (n < kSliceMinN) return 0;
+  const int64_t p = n / 16384 < kMaxSlices ? n / 16384 : kMaxSlices;
+  const int64_t lists = (rows < 64 ? rows : 64) * p;  // and at most 256, whatever the rows
+  return (size_t)(lists < 256 ? lists : 256) * sizeof(SliceList);
+}
+
 hipError_t launch_topk_rows(const float* scores, int64_t rows, int64_t n, int64_t ld, int k,
                             float* out_scores, int64_t* out_idx, void* scratch,
                             hipStream_t stream) {

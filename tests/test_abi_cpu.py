@@ -229,6 +229,39 @@ def test_dense_long_stores_keep_no_score_matrix(nq, n):
     assert lib.dense_ip_topk_workspace_size(1, 1 << 21, 64, 100) >= 4 << 21
 
 
+_SIZES_N = sorted({max(1, e + d) for e in (1000, 8192, 60_000, 65_536, 81_920, 131_072, 1_000_000,
+                                             1 << 20, 1 << 21, 8_400_000, 16_400_000, 60_000_000)
+                  for d in (-1, 0, 1)})
+_SIZES_NQ = sorted(set(range(1, 132)) | {200, 256, 257, 511, 512, 513, 1024, 4096})
+
+
+@pytest.mark.parametrize("dim,k", [(8, 1), (1024, 100), (64, 1000)])
+def test_dense_workspace_never_shrinks(dim, k):
+    # a workspace sized for a program's full batch serves its last, shorter one, and one sized for
+    # its longest store the others
+    f = hpr.lib().dense_ip_topk_workspace_size
+    sizes = [[f(nq, n, dim, k) for n in _SIZES_N] for nq in _SIZES_NQ]
+    for row in sizes:
+        assert all(a <= b for a, b in zip(row, row[1:]))
+    for col in zip(*sizes):
+        assert all(a <= b for a, b in zip(col, col[1:]))
+    for nq, row in zip(_SIZES_NQ, sizes):
+        for n, size in zip(_SIZES_N, row):
+            if n <= 131_072 or (n <= 1 << 21 and nq * n <= 1 << 26):
+                assert size >= 4 * nq * n
+            assert size <= f(nq, n, dim, k + 1)
+
+
+def test_maxsim_topk_workspace_never_shrinks():
+    f = hpr.lib().maxsim_topk_workspace_size
+    for n in _SIZES_N:
+        row = [f(nq, 32, n, 4 * n, 128, 10) for nq in _SIZES_NQ]
+        assert all(a <= b for a, b in zip(row, row[1:]))
+    for nq in (1, 3, 64, 65, 300):
+        col = [f(nq, 32, n, 4 * n, 128, 10) for n in _SIZES_N]
+        assert all(a <= b for a, b in zip(col, col[1:]))
+
+
 def test_csr_validate_and_scale_reject_null():
     lib = hpr.lib()
     bad = ctypes.c_int64(0)
