@@ -112,8 +112,16 @@ def _check(status):
         raise HprError(status, lib().hpr_last_error().decode())
 
 
+# The raw handle of a device's current stream, without the Stream object around it.  torch's accessor
+# for it is not public: where it is missing, the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    index = torch.cuda.current_device() if device.index is None else device.index
+    if _raw_stream is None:
+        return torch.cuda.current_stream(index).cuda_stream
+    return _raw_stream(index)
 
 
 def _launch(fn, device, *args):

@@ -281,3 +281,18 @@ def test_binding_refuses_cpu_tensors():
     with pytest.raises(ValueError):
         hpr.maxsim_score(Q, torch.zeros((1, 8), dtype=torch.bfloat16),
                          torch.tensor([0, 1], dtype=torch.int64))
+
+
+def test_stream_of_a_device_without_an_index(monkeypatch):
+    # "cuda" names the current device; the raw handle also comes without torch's private accessor
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda index: types.SimpleNamespace(cuda_stream=100 + index))
+    monkeypatch.setattr(hpr, "_raw_stream", lambda index: 200 + index)
+    assert hpr._stream(torch.device("cuda")) == 203
+    assert hpr._stream(torch.device("cuda:1")) == 201
+    monkeypatch.setattr(hpr, "_raw_stream", None)
+    assert hpr._stream(torch.device("cuda")) == 103
+    assert hpr._stream(torch.device("cuda:1")) == 101

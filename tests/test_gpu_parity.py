@@ -644,6 +644,11 @@ def test_calls_on_a_non_default_stream():
     assert torch.equal(ref, out)
 
 
+def test_calibrate_on_the_current_device():
+    low, rand, read = hpr.calibrate(device="cuda", mfma_iters=200, read_bytes=1 << 26, reps=1)
+    assert low > 0 and rand > 0 and read > 0
+
+
 def test_concurrent_calls_on_two_streams_with_separate_workspaces():
     # two streams, each with its own workspace, run different calls at the same time; the
     # results equal those of the same calls made one after the other on the default stream
