@@ -297,7 +297,8 @@ def _scaled_grads(dq, dd, scale):
     """bf16(dq * scale) and bf16(dd * scale) (either may be None) in one launch; dq and dd stay
     as they are.  The inputs of the losses are bf16, so this is what autograd hands on."""
     device = (dq if dq is not None else dd).device
-    src = [None if t is None else t.contiguous() for t in (dq, dd)]
+    # (a saved-tensor hook may hand back another type or layout than it was given)
+    src = [None if t is None else t.to(torch.float32).contiguous() for t in (dq, dd)]
     out = [None if t is None else torch.empty(t.shape, dtype=torch.bfloat16, device=device)
            for t in src]
     q, d = [0 if t is None else t.numel() for t in src]

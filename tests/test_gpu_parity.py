@@ -631,6 +631,25 @@ def test_autograd_second_backward_over_a_retained_graph():
         assert torch.equal(gd2, (-3.0 * r["dd"]).bfloat16())
 
 
+def test_autograd_saved_gradients_through_hooks():
+    # saved-tensor hooks that keep the gradients in 16 bits, or transposed, or on the host
+    w = synth.coltrast_step(seed=3, nq=4, n_neg=3, ld=32)
+    Q = w["Q"].to(DEV).requires_grad_(True)
+    D = w["D"].to(DEV).requires_grad_(True)
+    off, pos = _to_dev(w["off"], w["pos"])
+    r = hpr.coltrast_loss_fwd_bwd(Q.detach(), D.detach(), off, pos, 1.5625)
+    hooks = [(lambda t: t.to(torch.bfloat16), lambda t: t),
+             (lambda t: t.transpose(0, 1).contiguous(), lambda t: t.transpose(0, 1)),
+             (lambda t: t.cpu(), lambda t: t.to(DEV))]
+    for pack, unpack in hooks:
+        with torch.autograd.graph.saved_tensors_hooks(pack, unpack):
+            loss = hpr.coltrast_loss(Q, D, off, pos, 1.5625)
+        got = torch.autograd.grad(3.0 * loss, (Q, D))
+        for g, ref in zip(got, (r["dq"], r["dd"])):
+            kept = unpack(pack(ref)).float()
+            assert torch.equal(g, (3.0 * kept).bfloat16())
+
+
 # ------------------------------------------------------------------------------ plumbing
 
 def test_calls_on_a_non_default_stream():
