@@ -90,6 +90,15 @@ def source_sha(*names):
     return h.hexdigest()[:16]
 
 
+def dense_scored_rows(nq, n, k):
+    """(rows scored by the largest launch of a dense call, whether it stores the scores).  A store no
+    longer than the sample, or of at most 2^21 rows and 2^26 scores, is scored and stored whole; a
+    longer one has the rows past its sample filtered."""
+    sample = max(131072, 32 * k)
+    stored = n <= sample or (n <= 1 << 21 and nq * n <= 1 << 26)
+    return (n, True) if stored else (n - sample, False)
+
+
 def committed_traffic(kernel, workload, sha):
     """HBM bytes per launch from a committed rocprofv3 counter summary, if still current."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
@@ -256,10 +265,7 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
         def step():
             ws_out["scores"], ws_out["idx"] = hpr.dense_ip_topk(Q, X, k, ws=ws)
 
-        # the filtered scan covers the rows past the sample; a call of at most 2^26 scores scores
-        # and stores every row in one launch instead
-        stored = nq * n <= 1 << 26
-        scanned = float(n if stored else n - min(n, max(131072, 32 * k)))
+        scanned, stored = dense_scored_rows(nq, n, k)
         flops = 2.0 * dim * nq * scanned
 
         def cpu_sample():
@@ -300,7 +306,7 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
             r = hpr.retrieval_metrics(ws_out["idx"][pq].contiguous(), pr.contiguous(), k)
             m = r["metrics"].cpu().tolist()
             return {"queries": int(pq.numel()), "k": k, "p_at_k": m[0], "mrr_at_k": m[1]}
-        # that launch's algorithmic bytes: its rows and the queries read once, stored scores written
+        # the largest launch's algorithmic bytes: its rows and the queries read once, stored scores written
         sbytes = 2.0 * dim * (scanned + nq) + (4.0 * nq * n if stored else 0.0)
         return dict(step=step, pairs=nq, kernel="dense_sample" if stored else "dense_scan",
                     flops=flops, bytes=sbytes, after=after,

@@ -354,6 +354,24 @@ def test_dense_topk_select(nq, n, k, kind):
         assert np.array_equal(s[q] * 1024, sign * v[order])
 
 
+@pytest.mark.parametrize("nq,n,k", [(600, 131_072, 10), (2, 1 << 21, 10), (2, (1 << 21) + 1, 10),
+                                    (63, 1_065_220, 10), (63, 1_065_221, 10)])
+def test_bench_names_the_launch_that_scores(nq, n, k):
+    # the benchmark's FLOPs and times are those of the launch that ran: stored scores (here of a store
+    # no longer than the sample too, though they are more than 2^26), or the filtered scan
+    import bench
+    Q, X = _device_rows(nq, 8, 91), _device_rows(n, 8, 92)
+    hpr.kernel_timing(True)
+    for name in ("dense_sample", "dense_scan"):
+        hpr.kernel_timing_read(name)
+    hpr.dense_ip_topk(Q, X, k)
+    sample, scan = [hpr.kernel_timing_read(name)[1] for name in ("dense_sample", "dense_scan")]
+    hpr.kernel_timing(False)
+    rows, stored = bench.dense_scored_rows(nq, n, k)
+    assert (sample, scan) == (1, 0 if stored else 1)
+    assert rows == (n if stored else n - SAMPLE_ROWS) and stored != _filtered(nq, n)
+
+
 def _topk_us(Qd, Xd, k):
     hpr.dense_ip_topk(Qd, Xd, k)
     hpr.kernel_timing(True)
