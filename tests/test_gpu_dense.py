@@ -2,7 +2,7 @@
 
 The call has three regimes, each covered here:
   * the store is no larger than the exact sample, or all its scores are few enough to be kept
-    (at most 2^26): every row is scored and selected directly;
+    (at most 2^26, of at most 2^21 rows): every row is scored and selected directly;
   * the filter path: rows past the sample are kept only when they beat the sample's k-th score;
   * the exact fallback: a query whose candidate list overflows is queued on the device and its
     k-th key found by a radix select over rescans of the store, then its top-k collected; the
@@ -45,14 +45,54 @@ def _check_structure(s, i, n, k):
         assert np.all((a > b) | ((a == b) & (i[q, :-1] < i[q, 1:])))
 
 
+def _tile(filtered, nq, rows, dim, k):
+    """The GEMM tile of a launch, as the library chooses it (so that no case drifts off its line)."""
+    def grid(tq, tr):
+        return -(-nq // tq) * -(-rows // tr)
+    if nq > 128 and grid(256, 256) >= 144:
+        return "wide"
+    if filtered and 64 < nq <= 128 and nq * k > 192 * dim:
+        return "wide"
+    if nq > 64 and grid(128, 128) >= 384:
+        return "mid"
+    if nq > 32 and grid(64, 128) >= 300:
+        return "long" if filtered else "narrow"
+    if filtered and nq <= 32:
+        return "skinny" if dim >= 640 and dim & (dim - 1) and nq * k <= 5 * dim else "long"
+    if nq <= 32 and dim >= 4096 and rows * dim >= 3 << 29:
+        return "short"
+    return "skinny" if grid(32, 128) >= 192 else "short"
+
+
+def _filtered(nq, n):
+    return n > SAMPLE_ROWS and (n > 1 << 21 or nq * n > 1 << 26)
+
+
+def _device_rows(n, dim, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    X = torch.empty((n, dim), dtype=torch.float16, device=DEV)
+    step = (1 << 27) // dim
+    for r in range(0, n, step):
+        x = torch.randn((min(n - r, step), dim), generator=g, device=DEV)
+        X[r:r + step] = synth._normalise(x).to(torch.float16)
+    return X
+
+
+def _scores64(Q, X):
+    """The exact scores of device rows, in 64 bits, on the host."""
+    q, step = Q.double(), (1 << 27) // X.shape[1]
+    return torch.cat([q @ X[r:r + step].double().t().contiguous()
+                      for r in range(0, X.shape[0], step)], 1).cpu().numpy()
+
+
 @pytest.mark.parametrize("nq,n,dim,k", [
     (1, 1, 8, 1),          # smallest shapes
     (37, 5000, 200, 10),   # K tail (200 = 6 chunks of 32 + 8), ragged query and row tiles
     (300, 2048, 4096, 100),
     (5, 1000, 8192, 1000),  # largest dim; k = n
     (3, 777, 24, 777),
-    (64, 3000, 128, 10),   # the widest narrow (64-query) tile
-    (65, 3000, 136, 10),   # the narrowest wide (256-query) tile
+    (64, 3000, 128, 10),   # whole tiles of 32 queries
+    (65, 3000, 136, 10),   # one query past them
 ])
 def test_dense_topk_whole_store_sampled(nq, n, dim, k):
     Q, X = _rows(nq, dim, 1 + n), _rows(n, dim, 2 + n)
@@ -64,8 +104,8 @@ def test_dense_topk_whole_store_sampled(nq, n, dim, k):
 
 
 def test_dense_topk_filter_path_matches_oracle():
-    nq, n, dim, k = 300, 200_000, 96, 50
-    assert n > SAMPLE_ROWS
+    nq, n, dim, k = 300, 240_000, 96, 50
+    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
     Q, X = _rows(nq, dim, 11), _rows(n, dim, 12)
     s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
     s, i = s.cpu().numpy(), i.cpu().numpy()
@@ -87,19 +127,23 @@ def test_dense_topk_filter_path_matches_oracle():
 
 
 def test_dense_topk_filter_path_few_queries():
-    # at most 64 queries take the narrow tile in the sample and in the filtered scan
-    nq, n, dim, k = 17, 400_000, 256, 100
-    Q, X = _rows(nq, dim, 13), _rows(n, dim, 14)
-    s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
+    # the sample takes tiles of 32 queries, the filtered scan of 64
+    nq, n, dim, k = 17, 2_100_003, 256, 100
+    assert _filtered(nq, n)
+    assert _tile(False, nq, SAMPLE_ROWS, dim, k) == "skinny"
+    assert _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "long"
+    Q, X = _device_rows(nq, dim, 13), _device_rows(n, dim, 14)
+    s, i = hpr.dense_ip_topk(Q, X, k)
     s, i = s.cpu().numpy(), i.cpu().numpy()
     _check_structure(s, i, n, k)
-    O = oracle.dense_scores(_f16(Q), _f16(X))
+    O = _scores64(Q, X)
     for q in range(nq):
         check_topk(s[q], i[q], O[q], k, rel=REL)
 
 
 def test_dense_topk_overflowing_lists_take_the_exact_fallback():
-    nq, n, dim, k = 40, 150_000, 64, 20
+    nq, n, dim, k = 460, 150_000, 200, 20
+    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
     Q, X = _rows(nq, dim, 21), _rows(n, dim, 22)
     a0 = SAMPLE_ROWS + 100
     a1 = SAMPLE_ROWS + 5000
@@ -135,26 +179,31 @@ def _overflowing_store(nq, n, dim, copies, seed):
     return Q, X, a0
 
 
-def test_dense_topk_every_list_overflows():
-    # 70 queries: the scan takes the wide tile, the fallback two 64-query tiles
-    nq, n, dim, k = 70, 140_000, 64, 100
-    Q, X, a0 = _overflowing_store(nq, n, dim, 2500, 41)
-    s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
+@pytest.mark.parametrize("nq,n,copies,tile", [(70, 960_000, 4000, "mid"), (520, 150_000, 2500, "wide")])
+def test_dense_topk_every_list_overflows(nq, n, copies, tile):
+    # every query is queued: the fallback's rescans take two and nine 64-query tiles, over seven
+    # K stages (the last one ragged)
+    dim, k = 200, 100
+    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
+    Q, X, a0 = _overflowing_store(nq, n, dim, copies, 41)
+    Qd, Xd = Q.to(DEV), X.to(DEV)
+    s, i = hpr.dense_ip_topk(Qd, Xd, k)
     s, i = s.cpu().numpy(), i.cpu().numpy()
     _check_structure(s, i, n, k)
     for q in range(nq):
         assert i[q].tolist() == list(range(a0, a0 + k)), f"query {q}"
         assert np.all(s[q] == s[q, 0])
-    Qh, Xh = _f16(Q), _f16(X)
-    O = oracle.dense_scores(Qh[[0, 63, 64, 69]], Xh)
-    for r, q in enumerate((0, 63, 64, 69)):
+    pick = [0, 63, 64, nq - 1]
+    O = _scores64(Qd[pick], Xd)
+    for r, q in enumerate(pick):
         check_topk(s[q], i[q], O[r], k, rel=REL)
 
 
 def test_dense_topk_replays_in_a_hip_graph_with_overflow():
     # the whole call, the device-decided fallback included, is captured once and replayed with
     # eager work and synchronisation in between; every replay reproduces the eager result
-    nq, n, dim, k = 40, 150_000, 64, 20
+    nq, n, dim, k = 460, 150_000, 136, 20
+    assert _filtered(nq, n)
     Q, X = _rows(nq, dim, 21), _rows(n, dim, 22)
     a0 = SAMPLE_ROWS + 100
     X[a0:a0 + 3000] = Q[0]
@@ -179,15 +228,15 @@ def test_dense_topk_replays_in_a_hip_graph_with_overflow():
     assert gi[0].tolist() == list(range(a0, a0 + k))
 
 
-@pytest.mark.parametrize("nq,n,dim,k,copies", [
-    (520, 140_000, 16, 50, 0),         # filtered scan with wide tiles
-    (64, 1_100_000, 8, 20, 0),         # ... with narrow ones
-    (520, 140_000, 16, 20, 3000),      # two overflowing lists: the exact fallback
-    (64, 1_100_000, 8, 20, 5000),
+@pytest.mark.parametrize("nq,n,dim,k,copies,tile", [
+    (520, 150_000, 136, 50, 0, "wide"),
+    (64, 1_100_000, 72, 20, 0, "long"),
+    (520, 150_000, 136, 20, 3000, "wide"),  # two overflowing lists: the exact fallback
+    (64, 1_100_000, 72, 20, 5000, "long"),
 ])
-def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies):
+def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies, tile):
     # more than 2^26 scores: sample, filtered scan, merge, and the fallback for the overflowing lists
-    assert nq * n > 1 << 26 and n > SAMPLE_ROWS
+    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
     Q, X = _rows(nq, dim, 51 + nq), _rows(n, dim, 52 + nq)
     at = {0: SAMPLE_ROWS + 100, nq - 1: n - copies - 1}
     if copies:
@@ -223,45 +272,6 @@ def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies):
             check_topk(s[q], i[q], O[r], k, rel=REL)
 
 
-def _tile(filtered, nq, rows, dim, k):
-    """The GEMM tile of a launch, as the library chooses it (so that no case drifts off its line)."""
-    def grid(tq, tr):
-        return -(-nq // tq) * -(-rows // tr)
-    if nq > 128 and grid(256, 256) >= 144:
-        return "wide"
-    if filtered and 64 < nq <= 128 and nq * k > 192 * dim:
-        return "wide"
-    if nq > 64 and grid(128, 128) >= 384:
-        return "mid"
-    if nq > 32 and grid(64, 128) >= 300:
-        return "long" if filtered else "narrow"
-    if filtered and nq <= 32:
-        return "skinny" if dim >= 640 and dim & (dim - 1) and nq * k <= 5 * dim else "long"
-    if nq <= 32 and dim >= 4096 and rows * dim >= 3 << 29:
-        return "short"
-    return "skinny" if grid(32, 128) >= 192 else "short"
-
-
-def _filtered(nq, n):
-    return n > SAMPLE_ROWS and (n > 1 << 21 or nq * n > 1 << 26)
-
-
-def _device_rows(n, dim, seed):
-    g = torch.Generator(device=DEV).manual_seed(seed)
-    X = torch.empty((n, dim), dtype=torch.float16, device=DEV)
-    for r in range(0, n, 1 << 18):
-        x = torch.randn((min(n - r, 1 << 18), dim), generator=g, device=DEV)
-        X[r:r + (1 << 18)] = synth._normalise(x).to(torch.float16)
-    return X
-
-
-def _scores64(Q, X):
-    """The exact scores of device rows, in 64 bits, on the host."""
-    q = Q.double()
-    return torch.cat([q @ X[r:r + (1 << 18)].double().t().contiguous()
-                      for r in range(0, X.shape[0], 1 << 18)], 1).cpu().numpy()
-
-
 @pytest.mark.parametrize("nq,n,dim,k,tile", [
     (600, SAMPLE_ROWS + 48 * 256 - 3, 136, 20, "wide"),  # 144 of them; one fewer
     (600, SAMPLE_ROWS + 47 * 256, 136, 20, "mid"),
@@ -287,26 +297,29 @@ def test_dense_topk_filter_tiles(nq, n, dim, k, tile):
         check_topk(s[q], i[q], O[r], k, rel=REL)
 
 
-@pytest.mark.parametrize("nq,n,dim,k", [
-    (129, 18_400, 72, 10), (256, 18_177, 64, 10),   # 144 wide tiles, the last one ragged
-    (257, 12_000, 40, 10), (128, 49_100, 24, 10),    # one fewer; 384 mid tiles
-    (65, 49_025, 136, 10), (65, 48_900, 136, 10),
-    (33, 38_300, 200, 10), (64, 38_280, 8, 10),       # 300 narrow tiles and one fewer
-    (32, 24_500, 72, 10), (1, 24_449, 1032, 10), (33, 12_200, 128, 10),  # 192 skinny tiles
-    (31, 24_448, 72, 10), (1, 65, 4096, 10),          # short ones
-    (2, 196_608, 2048, 5), (32, 196_607, 64, 5),      # many rounds of long rows: short
+@pytest.mark.parametrize("nq,n,dim,k,tile", [
+    (129, 36_700, 72, 10, "wide"), (256, 36_609, 64, 10, "wide"), (257, 18_177, 40, 10, "wide"),  # 144
+    (129, 36_600, 72, 10, "mid"), (257, 18_176, 40, 10, "mid"),  # of them, and fewer
+    (128, 49_100, 24, 10, "mid"), (65, 49_025, 136, 10, "mid"), (65, 49_024, 136, 10, "narrow"),
+    (33, 38_300, 200, 10, "narrow"), (64, 38_273, 8, 10, "narrow"), (64, 38_272, 8, 10, "skinny"),
+    (32, 24_500, 72, 10, "skinny"), (1, 24_449, 1032, 10, "skinny"), (33, 12_200, 128, 10, "skinny"),
+    (31, 24_448, 72, 10, "short"), (1, 65, 4096, 10, "short"),
+    # many rounds of long rows
+    (2, 196_608, 8192, 5, "short"), (2, 196_607, 8192, 5, "skinny"), (32, 393_217, 4096, 5, "short"),
+    (32, 400_000, 4088, 5, "skinny"),
 ])
-def test_dense_topk_tile_choice(nq, n, dim, k):
+def test_dense_topk_tile_choice(nq, n, dim, k, tile):
     # both sides of every line between the GEMM's tiles, ragged in queries, rows and K
-    Q, X = _rows(nq, dim, 61 + n), _rows(n, dim, 62 + n)
+    assert not _filtered(nq, n) and _tile(False, nq, n, dim, k) == tile
+    Q, X = _device_rows(nq, dim, 61 + n), _device_rows(n, dim, 62 + n)
     X[n - 1], X[0] = Q[nq - 1], Q[0]  # the edges of the tiles hold winners
-    s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
+    s, i = hpr.dense_ip_topk(Q, X, k)
     s, i = s.cpu().numpy(), i.cpu().numpy()
     _check_structure(s, i, n, k)
     assert i[nq - 1, 0] == n - 1 or nq == 1
     assert 0 in i[0]
     pick = sorted({0, nq // 2, nq - 1})
-    O = oracle.dense_scores(_f16(Q[pick]), _f16(X))
+    O = _scores64(Q[pick], X)
     for r, q in enumerate(pick):
         check_topk(s[q], i[q], O[r], k, rel=REL)
 
