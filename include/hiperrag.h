@@ -214,12 +214,14 @@ hpr_status coltrast_total_loss_fwd_bwd(const uint16_t* q, int32_t nq, int32_t lq
  * metric"; Sec. 4.2; Sec. 2.3).  For L2-normalised rows the cosine is the inner product:
  *     s[q,n] = <Q[q,:], X[n,:]>  (fp16 x fp16 products, fp32 accumulation)
  * Results are sorted by score descending, equal scores by lower row index first.  Exact for any
- * input (no approximate index): the score matrix is never stored; rows past an exactly scored
- * sample are kept only when they beat the sample's k-th key, and a query whose candidate list
- * overflows the workspace's capacity (adversarial stores: thousands of rows above that key) is
- * finished on the device by a radix select over rescans of the store.  Like every call it is
- * asynchronous (no host synchronisation, no status decided on the device), so it can be
- * captured in a HIP graph; it never returns HPR_ERR_CAPACITY.
+ * input (no approximate index).  A call of at most 2^26 scores over at most 2^21 rows, or over a
+ * store no longer than the sample (131,072 rows), stores its scores in the workspace and selects
+ * from them.  Any other stores the sample's only: the rows past it are kept when they beat the
+ * sample's k-th key, and a query whose candidate list overflows the workspace's capacity
+ * (adversarial stores: thousands of rows above that key) is finished on the device by a radix
+ * select over rescans of the store.  Like every call it is asynchronous (no host synchronisation,
+ * no status decided on the device), so it can be captured in a HIP graph; it never returns
+ * HPR_ERR_CAPACITY.  Where a NaN score ranks is unspecified.
  *
  *   q   fp16 [nq, dim]; x fp16 [n, dim]; out_scores fp32 [nq, k]; out_idx int64 [nq, k].
  *   ws  workspace of dense_ip_topk_workspace_size(...) bytes.
@@ -274,7 +276,9 @@ hpr_status retrieval_metrics(const int64_t* topk_idx, int32_t nq, int32_t ld, in
                              const int64_t* positive, int32_t* ranks_out, double* metrics_out,
                              void* stream);
 
-/* Workspace sizes in bytes for the calls above (0 is a valid size only when stated). */
+/* Workspace sizes in bytes for the calls above (0 is a valid size only when stated).  Those of
+ * maxsim_topk, dense_ip_topk and semantic_chunk never fall as nq, n_docs or n grow: one workspace
+ * of a program's largest call holds its smaller ones. */
 size_t maxsim_score_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_t n_tok,
                                    int32_t dim);
 size_t maxsim_topk_workspace_size(int32_t nq, int32_t lq, int64_t n_docs, int64_t n_tok,
@@ -295,8 +299,8 @@ size_t semantic_chunk_workspace_size(int64_t n, int32_t dim);
 hpr_status hpr_csr_validate(const int64_t* d_off, int64_t n_docs, int64_t n_tok, void* ws,
                             void* stream, int64_t* h_first_bad_doc);
 
-/* hpr_scale_f32 -- x[i] *= *scale for i < n (scale is a device scalar); used to apply an
- * upstream gradient to the gradients of the loss calls without a host round trip. */
+/* hpr_scale_f32 -- x[i] *= *scale for i < n (scale is a device scalar): an upstream gradient
+ * applied to fp32 gradients of the loss calls in place, without a host round trip. */
 hpr_status hpr_scale_f32(float* x, int64_t n, const float* scale, void* stream);
 
 /* hpr_scale_grads_bf16 -- dq_out[i] = bf16(dq[i] * *scale) for i < n_q and dd_out[i] =
@@ -324,12 +328,14 @@ hpr_status hpr_read_calibration(const void* buf, int64_t bytes, uint32_t* sink, 
 
 /* Per-kernel timing for benchmarks.  While enabled, every kernel the library launches is
  * bracketed by two HIP events recorded on its launch stream.  hpr_kernel_timing_read
- * synchronises on the events recorded for kernel `name` ("partition", "maxsim",
- * "maxsim_argmax", "topk", "infonce", "pool", "contrastive", "grad_q", "grad_d",
- * "dense_sample", "dense_scan", "dense_merge", "dense_fallback", "semantic_chunk",
- * "retrieval_metrics",
- * "mfma_calibration", "read_calibration"), returns
- * the sum of their durations in milliseconds and the launch count, and forgets them. */
+ * synchronises on the events recorded for kernel `name` ("partition" (score calls of more than
+ * one round of workgroups), "maxsim", "maxsim_argmax", "topk", "infonce" (the L_LI call),
+ * "infonce_pool" (the total loss: InfoNCE and the pooling in one launch), "contrastive", "grad_q",
+ * "grad_d", "scale_grads", "dense_sample" (the sample's scores, or every score where they are all
+ * stored), "dense_scan", "dense_merge", "dense_fallback", "semantic_chunk", "retrieval_metrics",
+ * "mfma_calibration", "read_calibration"), returns the sum of their durations in milliseconds and
+ * the launch count (0 and 0 for any other name, such as "pool", which is no launch of its own any
+ * more), and forgets them. */
 hpr_status hpr_kernel_timing(int32_t enable);
 hpr_status hpr_kernel_timing_read(const char* name, double* total_ms, int64_t* launches);
 

@@ -317,7 +317,11 @@ __global__ __launch_bounds__(kMetricThreads) void metrics_kernel(
 // (mostly the host's) against 154 with 128 rows per wave.  Long ones take enough rows that the
 // re-read row before each range costs little: 400,000 x 4096 takes 637, 566, 564, 536 and 558 us
 // with 4, 8, 16, 32 and 64 rows (655 with 128, whose 3,125 waves fill the chip 1.02 times), and
-// 2,010,113 x 4096 takes 2.50 ms with 32 and 2.47 with 64 (2.54 with 128).
+// 2,010,113 x 4096 takes 2.50 ms with 32 and 2.47 with 64 (2.54 with 128).  The rule goes by the
+// sentences alone; over dims 64, 384, 768, 1024 and 4096 it is within 3 % of the best power of two
+// at 100,000 (dim 4096: 151 us, 135 with 64 rows), 400,000 and 2,000,000 sentences, and up to 5 us
+// off it between 12,000 and 30,000, where 8 or 16 rows are best: 12,288 x 768 16.7 us with 1 row,
+// 13.6 with 8; 30,000 x 768 19.0 with 4, 15.8 with 16; 12,288 x 4096 29.5 with 1, 23.8 with 4.
 int chunk_rows_per_wave(int64_t n) {
   int r = 1;
   while (r < 32 && n > (int64_t)r * 12288) r *= 2;

@@ -6,7 +6,7 @@
 // from them.  Otherwise the score matrix is never materialised:
 //
 //   1. Sample.  Rows [0, S) are scored exactly into a workspace matrix and the row top-k of it
-//      is taken (the radix select of topk.hip).  Its k-th score theta_q is a lower bound on the
+//      is taken (the select of topk.hip).  Its k-th score theta_q is a lower bound on the
 //      final k-th score, and every sample row outside the sample top-k is beaten by k sample
 //      rows, so it cannot be in the answer.
 //   2. Scan.  Rows [S, n) are scored by the GEMM kernel below, whose epilogue appends a row to

@@ -89,7 +89,8 @@ __device__ __forceinline__ uint32_t count_from(uint32_t c, TopkShared& s, uint32
 // want): a bound that at least `want` reach, lowered no further than to the lower edge of the
 // histogram bin that holds the want-th largest.  Narrowed until at most `most` entries reach it
 // (above + in <= most) or, with EXACT or when ties keep it from that, until it is the want-th
-// largest key itself (in: the entries equal to it).  At most three passes.
+// largest key itself (in: the entries equal to it).  At most four passes: one over the window where
+// the wanted entry lies below it, then 11 bits of the rest each (three for 32).
 template <bool EXACT, class Get>
 __device__ __forceinline__ Bound select_bound(Get get, int64_t m, uint32_t want, uint32_t most, uint32_t lo,
                               uint32_t hi, TopkShared& s) {

@@ -611,6 +611,15 @@ def test_scaled_gradients_equal_a_rounded_product(n_q, n_d, shift):
         assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
 
 
+@pytest.mark.parametrize("n", [1, 5, 1_000_003])
+def test_scale_in_place(n):
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn(n, generator=g).to(DEV)
+    scale = torch.tensor([-0.37], device=DEV)
+    ref = x * scale
+    assert hpr.scale_(x, scale) is x and torch.equal(x, ref)
+
+
 def test_autograd_second_backward_over_a_retained_graph():
     # each backward scales the forward's gradients by its own upstream gradient (the saved
     # tensors are not scaled in place, which would compound the two upstream gradients)
