@@ -472,9 +472,10 @@ __device__ __forceinline__ Winners slow_row(const float* x, int64_t n, uint32_t 
 }
 
 // One workgroup per row.  Bound by memory where the rows fill the chip (two workgroups per CU, which
-// is what 64 registers and 72 KiB of LDS are for): 4,096 rows of 131,072 in 377 us, 5.7 TB/s, k =
-// 100 (426 with an atomic and a key per streamed entry and fixed eight-bit digits); 1,024 rows of
-// 50,000 in 52 us (77).  A few rows are bound by the chain of steps and by their own CU's vector
+// is what 64 registers and 72 KiB of LDS are for): 4,096 rows of 131,072 in 387 us, 5.5 TB/s, k =
+// 100 (426 with an atomic and a key per streamed entry and fixed eight-bit digits; 377 to 381 with
+// sample runs of 64, whose cache lines are a quarter as many); 1,024 rows of 50,000 in 55 us (79).  A
+// few rows are bound by the chain of steps and by their own CU's vector
 // instructions: 20,000 entries in 11.6 us at k = 100 and 15.3 at k = 1000 (18.4 and 28.9), 8,000 in
 // 9.7 and 12.3 (15.4 and 25.8).
 __global__ __launch_bounds__(kThreads, 8) void topk_rows_kernel(const float* __restrict__ S,
