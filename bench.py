@@ -90,13 +90,16 @@ def source_sha(*names):
     return h.hexdigest()[:16]
 
 
-def dense_scored_rows(nq, n, k):
+def dense_scored_rows(nq, n, dim, k):
     """(rows scored by the largest launch of a dense call, whether it stores the scores).  A store no
-    longer than the sample, or of at most 2^21 rows and 2^26 scores, is scored and stored whole; a
-    longer one has the rows past its sample filtered."""
-    sample = max(131072, 32 * k)
-    stored = n <= sample or (n <= 1 << 21 and nq * n <= 1 << 26)
-    return (n, True) if stored else (n - sample, False)
+    longer than the sample is scored and stored whole, and so are calls of few enough scores (the
+    library's dense_stores); any other has the rows past its sample filtered."""
+    past = n - max(131072, 32 * k)
+    most = 9 << 22 if dim < 256 else 5 << 22 if dim < 2048 else 1 << 24
+    k_most = 64 + dim // 6
+    stored = past <= 0 or (n <= 1 << 21 and nq * n <= 1 << 26 and
+                           (nq > 128 or k >= k_most or nq * past * (k_most - k) <= most * k_most))
+    return (n, True) if stored else (past, False)
 
 
 def committed_traffic(kernel, workload, sha):
@@ -265,7 +268,7 @@ def build_workload(name, dev, scale, tau, nq_sub=None):
         def step():
             ws_out["scores"], ws_out["idx"] = hpr.dense_ip_topk(Q, X, k, ws=ws)
 
-        scanned, stored = dense_scored_rows(nq, n, k)
+        scanned, stored = dense_scored_rows(nq, n, dim, k)
         flops = 2.0 * dim * nq * scanned
 
         def cpu_sample():

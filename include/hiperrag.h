@@ -214,10 +214,10 @@ hpr_status coltrast_total_loss_fwd_bwd(const uint16_t* q, int32_t nq, int32_t lq
  * metric"; Sec. 4.2; Sec. 2.3).  For L2-normalised rows the cosine is the inner product:
  *     s[q,n] = <Q[q,:], X[n,:]>  (fp16 x fp16 products, fp32 accumulation)
  * Results are sorted by score descending, equal scores by lower row index first.  Exact for any
- * input (no approximate index).  A call of at most 2^26 scores over at most 2^21 rows, or over a
- * store no longer than the sample (131,072 rows), stores its scores in the workspace and selects
- * from them.  Any other stores the sample's only: the rows past it are kept when they beat the
- * sample's k-th key, and a query whose candidate list overflows the workspace's capacity
+ * input (no approximate index).  A call over a store no longer than the sample (131,072 rows), or of
+ * few enough scores (at most 2^26, over at most 2^21 rows), stores its scores in the workspace and
+ * selects from them.  Any other stores the sample's only: the rows past it are kept when they beat
+ * the sample's k-th key, and a query whose candidate list overflows the workspace's capacity
  * (adversarial stores: thousands of rows above that key) is finished on the device by a radix
  * select over rescans of the store.  Like every call it is asynchronous (no host synchronisation,
  * no status decided on the device), so it can be captured in a HIP graph; it never returns

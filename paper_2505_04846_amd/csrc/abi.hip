@@ -544,7 +544,7 @@ size_t dense_ip_topk_workspace_size(int32_t nq, int64_t n, int32_t dim, int32_t 
   if (stored > kDenseStoreAll) stored = kDenseStoreAll;
   if (stored < nq * whole) stored = nq * whole;
   const size_t most = align_up((size_t)stored * sizeof(float)) + align_up(topk_scratch_most(nq, n));
-  const DensePlan p = dense_plan(nq, n, k);
+  const DensePlan p = dense_plan(nq, n, dim, k);
   if (p.S == n) return most;
   size_t b = align_up((size_t)nq * (size_t)p.S * sizeof(float)) +  // sample scores
              align_up(topk_scratch_most(nq, p.S));
@@ -583,7 +583,7 @@ hpr_status dense_ip_topk(const uint16_t* q, int32_t nq, const uint16_t* x, int64
   hpr_status st = current_cu_count(&n_cu);
   if (st != HPR_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const DensePlan p = dense_plan(nq, n, k);
+  const DensePlan p = dense_plan(nq, n, dim, k);
   Carver c(ws);
   float* sample = c.take<float>((size_t)nq * (size_t)p.S * sizeof(float));
   void* scratch = c.take<char>(topk_scratch_bytes(nq, p.S));

@@ -1,9 +1,9 @@
 // Exact inner-product top-k over a dense fp16 store (pooled single-vector retrieval).
 //
 // s[q, r] = <Q[q], X[r]> (fp16 MFMA, fp32 accumulate); the k best rows per query under
-// (score desc, row asc).  Calls of few scores (dense_plan: the store no longer than the sample
-// below, or at most kDenseStoreAll scores of at most kDenseStoreRows rows) store them all and select
-// from them.  Otherwise the score matrix is never materialised:
+// (score desc, row asc).  Calls over a store no longer than the sample below, and others of few
+// scores (dense_stores), store them all and select from them.  Otherwise the score matrix is never
+// materialised:
 //
 //   1. Sample.  Rows [0, S) are scored exactly into a workspace matrix and the row top-k of it
 //      is taken (the select of topk.hip).  Its k-th score theta_q is a lower bound on the

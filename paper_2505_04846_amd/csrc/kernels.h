@@ -122,14 +122,22 @@ hipError_t launch_scale_grads(const float* dq, int64_t n_q, uint16_t* dq_out, co
 
 // Dense inner-product top-k ----------------------------------------------------------------------
 // Rows [0, S) are the exact sample; candidate lists hold `cap` entries per query.
-// Up to kDenseStoreAll scores (256 MiB) are all stored and selected from: the sample's filter and
-// the idle launches of the exact fallback cost about 110 us a call, the scores' two trips less
-// (150 queries x 400,000 rows x 384: 221 us against 236; 200 queries: 234 either way).
-// Not past kDenseStoreRows rows: the select takes its bound from the 16th of 16,384 sampled keys or
-// a later one, so about n / 1024 entries reach it, a quarter of its list's 8,192 places at 2^21 rows
-// (with k above 512 a half), all of them at 8.4 million; a row whose list overflows is walked whole by
-// one workgroup.  One query, dim 64, k = 100: 2,097,152 rows 105 us stored, 200 filtered; 8 million
-// 18.0 ms against 0.58; 60 million 134 against 3.9.
+// A call's scores are all stored and selected from, or the sample's only and the rows past it filtered
+// (dense_stores).
+//   At most kDenseStoreAll scores (256 MiB).
+//   Not past kDenseStoreRows rows: the select takes its bound from the 16th of 16,384 sampled keys or
+//   a later one, so about n / 1024 entries reach it, a quarter of its list's 8,192 places at 2^21 rows
+//   (with k above 512 a half), all of them at 8.4 million; a row whose list overflows is walked whole
+//   by one workgroup.  One query, dim 64, k = 100: 2,097,152 rows 105 us stored, 200 filtered; 8
+//   million 18.0 ms against 0.58; 60 million 134 against 3.9.
+//   Within these, storing saves the filter's idle fallback launches (about 55 us) and its appends to
+//   the candidate lists (1 to 4 ns each, about k (n - S) / S a query), and costs two trips of the
+//   scores past the sample, dearer the longer the rows are.  Up to 128 queries the line is where the
+//   two meet, from 1,625 calls of both kinds at dim 8 to 8192, 2 to 256 queries, 200,000 to 2,097,152
+//   rows, k = 1 to 300 (us, stored and filtered): 64 x 524,288 x 1024 at k = 10 273, 268, and 64 x
+//   1,048,576 529, 448, at k = 1000 541, 1077; 32 x 1,048,576 x 64 at k = 10 95, 116, 32 x 2,097,152
+//   187, 166; 43 x 390,167 x 4096 612, 623, 43 x 780,335 1247, 1160.  More queries multiply in 256 x
+//   256 tiles, which hide the stores: 200 x 335,544 x 1024 at k = 10 295, 323, x 64 121, 138.
 constexpr int64_t kDenseStoreAll = (int64_t)1 << 26;
 constexpr int64_t kDenseStoreRows = (int64_t)1 << 21;
 struct DensePlan {
@@ -139,11 +147,17 @@ struct DensePlan {
 inline int64_t dense_sample_rows(int k) {
   return (int64_t)32 * k > 131072 ? (int64_t)32 * k : 131072;
 }
-inline DensePlan dense_plan(int nq, int64_t n, int k) {
+inline bool dense_stores(int nq, int64_t n, int dim, int k) {
+  const int64_t past = n - dense_sample_rows(k);
+  if (past <= 0) return true;
+  if (n > kDenseStoreRows || nq * n > kDenseStoreAll) return false;
+  const int64_t most = dim < 256 ? (int64_t)9 << 22 : dim < 2048 ? (int64_t)5 << 22 : (int64_t)1 << 24;
+  const int64_t k_most = 64 + dim / 6;  // from here on the appends alone cost more than the stores
+  return nq > 128 || k >= k_most || nq * past * (k_most - k) <= most * k_most;
+}
+inline DensePlan dense_plan(int nq, int64_t n, int dim, int k) {
   DensePlan p;
-  const int64_t target = dense_sample_rows(k);
-  const bool store_all = n <= kDenseStoreRows && (int64_t)nq * n <= kDenseStoreAll;
-  p.S = n < target || store_all ? n : target;
+  p.S = dense_stores(nq, n, dim, k) ? n : dense_sample_rows(k);
   if (p.S == n) {
     p.cap = 0;
   } else {

@@ -2,7 +2,8 @@
 
 The call has three regimes, each covered here:
   * the store is no larger than the exact sample, or all its scores are few enough to be kept
-    (at most 2^26, of at most 2^21 rows): every row is scored and selected directly;
+    (at most 2^26, of at most 2^21 rows, and fewer where filtering them is the faster way): every
+    row is scored and selected directly;
   * the filter path: rows past the sample are kept only when they beat the sample's k-th score;
   * the exact fallback: a query whose candidate list overflows is queued on the device and its
     k-th key found by a radix select over rescans of the store, then its top-k collected; the
@@ -64,8 +65,16 @@ def _tile(filtered, nq, rows, dim, k):
     return "skinny" if grid(32, 128) >= 192 else "short"
 
 
-def _filtered(nq, n):
-    return n > SAMPLE_ROWS and (n > 1 << 21 or nq * n > 1 << 26)
+def _filtered(nq, n, dim, k):
+    """Whether a call filters the rows past its sample; otherwise it stores every score."""
+    past = n - SAMPLE_ROWS
+    if past <= 0:
+        return False
+    if n > 1 << 21 or nq * n > 1 << 26:
+        return True
+    most = 9 << 22 if dim < 256 else 5 << 22 if dim < 2048 else 1 << 24
+    k_most = 64 + dim // 6
+    return nq <= 128 and k < k_most and nq * past * (k_most - k) > most * k_most
 
 
 def _device_rows(n, dim, seed):
@@ -105,7 +114,7 @@ def test_dense_topk_whole_store_sampled(nq, n, dim, k):
 
 def test_dense_topk_filter_path_matches_oracle():
     nq, n, dim, k = 300, 240_000, 96, 50
-    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
+    assert _filtered(nq, n, dim, k) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
     Q, X = _rows(nq, dim, 11), _rows(n, dim, 12)
     s, i = hpr.dense_ip_topk(Q.to(DEV), X.to(DEV), k)
     s, i = s.cpu().numpy(), i.cpu().numpy()
@@ -129,7 +138,7 @@ def test_dense_topk_filter_path_matches_oracle():
 def test_dense_topk_filter_path_few_queries():
     # the sample takes tiles of 32 queries, the filtered scan of 64
     nq, n, dim, k = 17, 2_100_003, 256, 100
-    assert _filtered(nq, n)
+    assert _filtered(nq, n, dim, k)
     assert _tile(False, nq, SAMPLE_ROWS, dim, k) == "skinny"
     assert _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "long"
     Q, X = _device_rows(nq, dim, 13), _device_rows(n, dim, 14)
@@ -143,7 +152,7 @@ def test_dense_topk_filter_path_few_queries():
 
 def test_dense_topk_overflowing_lists_take_the_exact_fallback():
     nq, n, dim, k = 460, 150_000, 200, 20
-    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
+    assert _filtered(nq, n, dim, k) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == "wide"
     Q, X = _rows(nq, dim, 21), _rows(n, dim, 22)
     a0 = SAMPLE_ROWS + 100
     a1 = SAMPLE_ROWS + 5000
@@ -184,7 +193,7 @@ def test_dense_topk_every_list_overflows(nq, n, copies, tile):
     # every query is queued: the fallback's rescans take two and nine 64-query tiles, over seven
     # K stages (the last one ragged)
     dim, k = 200, 100
-    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
+    assert _filtered(nq, n, dim, k) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
     Q, X, a0 = _overflowing_store(nq, n, dim, copies, 41)
     Qd, Xd = Q.to(DEV), X.to(DEV)
     s, i = hpr.dense_ip_topk(Qd, Xd, k)
@@ -203,7 +212,7 @@ def test_dense_topk_replays_in_a_hip_graph_with_overflow():
     # the whole call, the device-decided fallback included, is captured once and replayed with
     # eager work and synchronisation in between; every replay reproduces the eager result
     nq, n, dim, k = 460, 150_000, 136, 20
-    assert _filtered(nq, n)
+    assert _filtered(nq, n, dim, k)
     Q, X = _rows(nq, dim, 21), _rows(n, dim, 22)
     a0 = SAMPLE_ROWS + 100
     X[a0:a0 + 3000] = Q[0]
@@ -236,7 +245,7 @@ def test_dense_topk_replays_in_a_hip_graph_with_overflow():
 ])
 def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies, tile):
     # more than 2^26 scores: sample, filtered scan, merge, and the fallback for the overflowing lists
-    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
+    assert _filtered(nq, n, dim, k) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
     Q, X = _rows(nq, dim, 51 + nq), _rows(n, dim, 52 + nq)
     at = {0: SAMPLE_ROWS + 100, nq - 1: n - copies - 1}
     if copies:
@@ -284,7 +293,7 @@ def test_dense_topk_past_the_stored_scores(nq, n, dim, k, copies, tile):
 ])
 def test_dense_topk_filter_tiles(nq, n, dim, k, tile):
     # the filter of every tile, on both sides of the lines between them, over several K stages
-    assert _filtered(nq, n) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
+    assert _filtered(nq, n, dim, k) and _tile(True, nq, n - SAMPLE_ROWS, dim, k) == tile
     Q, X = _device_rows(nq, dim, 81 + nq), _device_rows(n, dim, 82 + dim)
     X[n - 1], X[SAMPLE_ROWS] = Q[nq - 1], Q[0]  # the edges of the scan hold winners
     s, i = hpr.dense_ip_topk(Q, X, k)
@@ -310,7 +319,7 @@ def test_dense_topk_filter_tiles(nq, n, dim, k, tile):
 ])
 def test_dense_topk_tile_choice(nq, n, dim, k, tile):
     # both sides of every line between the GEMM's tiles, ragged in queries, rows and K
-    assert not _filtered(nq, n) and _tile(False, nq, n, dim, k) == tile
+    assert not _filtered(nq, n, dim, k) and _tile(False, nq, n, dim, k) == tile
     Q, X = _device_rows(nq, dim, 61 + n), _device_rows(n, dim, 62 + n)
     X[n - 1], X[0] = Q[nq - 1], Q[0]  # the edges of the tiles hold winners
     s, i = hpr.dense_ip_topk(Q, X, k)
@@ -367,22 +376,30 @@ def test_dense_topk_select(nq, n, k, kind):
         assert np.array_equal(s[q] * 1024, sign * v[order])
 
 
-@pytest.mark.parametrize("nq,n,k", [(600, 131_072, 10), (2, 1 << 21, 10), (2, (1 << 21) + 1, 10),
-                                    (63, 1_065_220, 10), (63, 1_065_221, 10)])
-def test_bench_names_the_launch_that_scores(nq, n, k):
-    # the benchmark's FLOPs and times are those of the launch that ran: stored scores (here of a store
-    # no longer than the sample too, though they are more than 2^26), or the filtered scan
+@pytest.mark.parametrize("nq,n,dim,k,stored", [
+    (600, 131_072, 8, 10, True),  # no longer than the sample, though more than 2^26 scores
+    (2, 1 << 21, 8, 10, True), (2, (1 << 21) + 1, 8, 10, False),
+    (129, 520_222, 16, 10, True), (129, 520_224, 16, 10, False),  # 2^26 scores
+    (129, 520_222, 2048, 1, True), (128, 262_144, 2048, 1, True), (128, 262_870, 2048, 1, False),
+    (64, 788_000, 200, 10, True), (64, 790_000, 200, 10, False), (64, 790_000, 200, 97, True),
+    (32, 850_000, 256, 10, True), (32, 855_000, 256, 10, False),
+])
+def test_bench_names_the_launch_that_scores(nq, n, dim, k, stored):
+    # every line between the stored scores and the filter; the benchmark's FLOPs and times are those
+    # of the launch that ran; either way the lists are exact
     import bench
-    Q, X = _device_rows(nq, 8, 91), _device_rows(n, 8, 92)
+    Q, X = _device_rows(nq, dim, 91), _device_rows(n, dim, 92)
     hpr.kernel_timing(True)
     for name in ("dense_sample", "dense_scan"):
         hpr.kernel_timing_read(name)
-    hpr.dense_ip_topk(Q, X, k)
+    s, i = hpr.dense_ip_topk(Q, X, k)
     sample, scan = [hpr.kernel_timing_read(name)[1] for name in ("dense_sample", "dense_scan")]
     hpr.kernel_timing(False)
-    rows, stored = bench.dense_scored_rows(nq, n, k)
     assert (sample, scan) == (1, 0 if stored else 1)
-    assert rows == (n if stored else n - SAMPLE_ROWS) and stored != _filtered(nq, n)
+    assert bench.dense_scored_rows(nq, n, dim, k) == (n if stored else n - SAMPLE_ROWS, stored)
+    assert stored != _filtered(nq, n, dim, k)
+    O = _scores64(Q[nq - 1:], X)
+    check_topk(s[nq - 1].cpu().numpy(), i[nq - 1].cpu().numpy(), O[0], k, rel=REL)
 
 
 def _topk_us(Qd, Xd, k):
