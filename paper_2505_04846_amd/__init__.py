@@ -112,27 +112,30 @@ def _check(status):
         raise HprError(status, lib().hpr_last_error().decode())
 
 
+def _public_raw_stream(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
 # The raw handle of a device's current stream, without the Stream object around it.  torch's accessor
 # for it is not public: where it is missing, the public way.
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _public_raw_stream)
 
 
 def _stream(device):
-    index = torch.cuda.current_device() if device.index is None else device.index
-    if _raw_stream is None:
-        return torch.cuda.current_stream(index).cuda_stream
-    return _raw_stream(index)
+    index = device.index
+    return _raw_stream(torch.cuda.current_device() if index is None else index)
 
 
 def _launch(fn, device, *args):
     """fn(*args, stream) with `device` current and its current stream last; raises on a status.
     Entering torch's device guard costs about as much as a kernel launch, so only a call for
     another device than the current one does."""
-    if torch.cuda.current_device() == device.index:
-        status = fn(*args, _stream(device))
+    index = device.index  # (a tensor's device always has one)
+    if torch.cuda.current_device() == index:
+        status = fn(*args, _raw_stream(index))
     else:
         with torch.cuda.device(device):
-            status = fn(*args, _stream(device))
+            status = fn(*args, _raw_stream(index))
     if status != 0:
         _check(status)
 
@@ -298,7 +301,8 @@ def _scaled_grads(dq, dd, scale):
     as they are.  The inputs of the losses are bf16, so this is what autograd hands on."""
     device = (dq if dq is not None else dd).device
     # (a saved-tensor hook may hand back another type or layout than it was given)
-    src = [None if t is None else t.to(torch.float32).contiguous() for t in (dq, dd)]
+    src = [t if t is None or (t.dtype == torch.float32 and t.is_contiguous())
+           else t.to(torch.float32).contiguous() for t in (dq, dd)]
     out = [None if t is None else torch.empty(t.shape, dtype=torch.bfloat16, device=device)
            for t in src]
     q, d = [0 if t is None else t.numel() for t in src]

@@ -290,9 +290,7 @@ def test_stream_of_a_device_without_an_index(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
     monkeypatch.setattr(torch.cuda, "current_stream",
                         lambda index: types.SimpleNamespace(cuda_stream=100 + index))
-    monkeypatch.setattr(hpr, "_raw_stream", lambda index: 200 + index)
-    assert hpr._stream(torch.device("cuda")) == 203
-    assert hpr._stream(torch.device("cuda:1")) == 201
-    monkeypatch.setattr(hpr, "_raw_stream", None)
-    assert hpr._stream(torch.device("cuda")) == 103
-    assert hpr._stream(torch.device("cuda:1")) == 101
+    for raw, base in ((lambda index: 200 + index, 200), (hpr._public_raw_stream, 100)):
+        monkeypatch.setattr(hpr, "_raw_stream", raw)
+        assert hpr._stream(torch.device("cuda")) == base + 3
+        assert hpr._stream(torch.device("cuda:1")) == base + 1
